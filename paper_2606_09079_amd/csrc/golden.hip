@@ -13,28 +13,45 @@
 // does not matter, and a set reaches p = num / den when
 // (its mass) * den >= num * Z in 128-bit integers.
 //
-// golden_row_kernel -- one 512-thread workgroup per (step, layer) row, three
-//   passes over the row: (1) the maximum; (2) a 4096-bin LDS histogram of the
-//   masses by the top 12 bits of each logit's order key, whose descending
-//   scan finds the bin where the cumulative mass reaches p; (3) the row's
-//   membership bitmap for the bins above it (wavefront ballots), the entries
-//   of that bin staged in LDS.  Two 10-bit digit rounds over the staged
-//   entries give the exact threshold key T and the number of entries equal to
-//   T that the set needs (those with the lowest indices).  A bin with more
-//   entries than LDS holds is refined by passes over the row instead.  The
-//   first two passes read through the caches (the next pass finds part of the
-//   row in the Infinity Cache); the last one streams.
-// golden_vote_kernel -- one thread per (sequence, step, bitmap word): the
-//   votes of the L layers for 32 entries as bit-sliced counters, the theta
-//   test, an OR into the label bitmap and the golden-set size.
+// golden_scan_kernel -- rows of more than 2,048 entries: one 512-thread
+//   workgroup per slice of at most 16,384 entries, which is read once into
+//   registers.  It leaves the slice's largest entries (every entry with a key
+//   at or above the slice's threshold, about 130 of 16,384), its maximum and
+//   the sum of the approximate weights of all other entries in the row's own
+//   bitmap words, which the next kernels overwrite.
+// golden_row_kernel -- one 256-thread workgroup per (step, layer) row takes in
+//   the listed entries (or the whole row up to 2,048 entries).  Their masses
+//   are exact; the mass of all other entries lies in an interval that bounds
+//   every rounding of the approximate sum.  A 1024-bin LDS histogram of the
+//   listed masses finds the bin where the cumulative mass reaches p, and the
+//   few entries in it are ranked by one wavefront: the threshold key T and the
+//   number of entries equal to T that the set needs.  When both ends of the
+//   interval give the same answer it is the exact one, and the row's bitmap is
+//   assembled in LDS.
+// golden_general_kernel -- the rows left open (flat ones, whose set reaches
+//   below the listed entries; many equal logits at the boundary; a boundary
+//   inside the interval) are read twice more: a 4096-bin LDS histogram of the
+//   exact masses by the top 12 bits of each logit's order key, whose descending
+//   scan finds the bin where the cumulative mass reaches p, then the bitmap of
+//   the bins above it (wavefront ballots) with the entries of that bin staged
+//   in LDS (or refined by passes over the row when they do not fit), and two
+//   10-bit digit rounds over them.
+// golden_vote_kernel -- one thread per (sequence, two steps, bitmap word):
+//   the votes of the L layers for 32 entries as bit-sliced counters, the theta
+//   test, an OR into the label bitmap and the golden-set sizes.
 // golden_compact_kernel -- one workgroup per sequence: label bitmap to
 //   ascending entry ids.
+//
+// One 64-step, 21-layer window of 131,072 entries (705 MB of logits) took 452 us
+// when the row kernel read every row three times; it takes 165 us now (scan 120,
+// rows 27, general path 4.5 with no row left to it, votes 9, labels 5), and about
+// 260 us for the one window in ten that leaves a row to the general path.
 #include "lsa_internal.h"
 
 namespace lsa {
 namespace {
 
-constexpr int kThreads = 512;   // three rows per compute unit at a time
+constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kBins = 4096;     // first digit: top 12 bits of the order key
 constexpr int kSubBins = 1024;  // two more digits of 10 bits
@@ -42,6 +59,9 @@ constexpr int kBinsPerThread = kBins / kThreads;
 constexpr int kSubPerThread = kSubBins / kThreads;
 constexpr int kCand = 1024;     // entries of the threshold bin staged in LDS
 constexpr int kUnroll = 16;     // 64-entry groups per wavefront per round
+constexpr int kScanVec = kGoldenSliceVecs / kThreads;  // float4s of a slice a thread holds
+constexpr int kSliceListMax = 340;    // entries a slice lists at most
+constexpr int kGoldenSlots = 3072;    // listed entries of a row the row kernel takes in
 
 struct u128 {
   uint64_t hi, lo;
@@ -118,56 +138,592 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_to
   return before + incl - v;
 }
 
-__global__ void __launch_bounds__(kThreads)
+// What golden_scan_kernel leaves of a slice, in 32-bit words at the slice's
+// share of the row's bitmap: the maximum m (float), the threshold key, the sum
+// of the other entries' weights 2^(x c - m c) (float), the number of listed
+// entries, then `cap` values and `cap` 16-bit entry numbers within the slice.
+constexpr int kSliceHead = 4;
+constexpr float kLog2e = 1.44269502f;  // c
+
+// Geometry of the ns slices of a row: the slice's words of the row's bitmap
+// and how many entries it can list, the same for every slice of a row.
+__device__ __forceinline__ int slice_words(int words, int ns) { return words / ns; }
+__device__ __forceinline__ int slice_cap(int words, int ns) {
+  return min((slice_words(words, ns) - kSliceHead) * 2 / 3, min(kGoldenSlots / ns, kSliceListMax));
+}
+// Scale of a slice's sum: weight of entry x is 2^(x c + off), off rounded to float32.
+__device__ __forceinline__ float slice_off(float m) { return m == -INFINITY ? 0.f : -(m * kLog2e); }
+
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float fmin2(float a, float b) { return a < b ? a : b; }
+__device__ __forceinline__ float fmax2(float a, float b) { return a > b ? a : b; }
+
+// The value of lane i ^ 1, of lane i ^ 2, and (once four, eight adjacent lanes
+// agree) of the other four of eight and the other eight of sixteen lanes.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+
+// op of this lane's value and that of lane ^ 16
+template <class Op>
+__device__ __forceinline__ float with16(float x, Op op) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// A workgroup barrier for data in LDS only (a fenced one also waits for memory).
+__device__ __forceinline__ void lds_barrier() {
+  constexpr int kWaitLds = 0xF | (0x3 << 14) | (0x7 << 4);  // s_waitcnt lgkmcnt(0)
+  __asm__ volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(kWaitLds);
+  __builtin_amdgcn_s_barrier();
+  __asm__ volatile("" ::: "memory");
+}
+
+// Bound: one read of the logits (HBM), against about ten vector instructions
+// per entry (an exponential among them).  The slice stays in registers, so the
+// maximum, the threshold and the sum need no second read; four workgroups per
+// CU overlap one's loads with another's arithmetic.  705 MB in 120 us, 5.9
+// TB/s; without the listing 114 us.  (Listing straight to memory took 138 us,
+// one wavefront per 4,096 entries with no barriers 208 us, and a persistent
+// grid that prefetches the next slice 169 us.)  The threshold is the
+// smallest of 32 group maxima (512 entries each), which about 130 entries of
+// 16,384 reach whatever their distribution; where those do not fit the list
+// (short slices, many equal logits) 16, 8, 4 or 2 groups raise it, and past
+// those nothing is listed and the threshold lies above the slice's maximum.
+__global__ void __launch_bounds__(kThreads, 8)
+golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
+  __shared__ float list_x[kWaves][kSliceListMax];
+  __shared__ uint16_t list_i[kWaves][kSliceListMax];
+  __shared__ float group_max[32];
+  __shared__ uint32_t wave_cnt[kWaves];
+  __shared__ double wave_sum[kWaves];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int id = blockIdx.x;
+  // sequence of this slice: the last b whose first slice is not past it
+  int b = 0;
+  for (int step = 32; step > 0; step >>= 1)
+    if (b + step < gt.batch && gt.scan_off[b + step] <= (int64_t)id) b += step;
+  const int ns = gt.slices[b], n = gt.n[b], words = gt.words[b], vps = gt.slice_vecs[b];
+  const int local = (int)(id - gt.scan_off[b]);
+  const int row = local / ns, sl = local - row * ns;
+  const int64_t first = gt.logit_off[b] + (int64_t)row * n;
+  const int lead = (int)(first & 3);  // the row starts `lead` entries into a float4
+  const int v0 = sl * vps, v1 = min(v0 + vps, (n + lead + 3) >> 2);
+  const float* p0 = a.logits + (first - lead) + 4 * (int64_t)v0;
+
+  // float4 v holds entries 4 v - lead .. + 3 of the row; the last one of a row
+  // may reach past its end and is read entry by entry.  The buffer ends with
+  // the slice's whole float4s: loads past it return 0, which -inf replaces.
+  f32x4 x[kScanVec];
+  const int have = min(v1, (n + lead) / 4) - v0;
+  {
+    constexpr int kNontemporal = 2;  // the nt bit of a buffer instruction's cache policy
+    const __amdgpu_buffer_rsrc_t src =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p0), (short)0, have * 16, 0x00020000);
+#pragma unroll
+    for (int j = 0; j < kScanVec; ++j) {
+      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+      const u32x4 y = __builtin_amdgcn_raw_buffer_load_b128(src, 16 * tid, 16 * kThreads * j, kNontemporal);
+      x[j] = __builtin_bit_cast(f32x4, y);
+    }
+  }
+  if (have < kGoldenSliceVecs) {  // uniform
+    const int left = n + lead - 4 * (v0 + have);  // entries of the row past them, in this slice if have < v1 - v0
+    const float* p = p0 + 4 * have;
+    f32x4 last = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (have < v1 - v0) {
+      last.x = p[0];
+      if (left > 1) last.y = p[1];
+      if (left > 2) last.z = p[2];
+    }
+#pragma unroll
+    for (int j = 0; j < kScanVec; ++j) {
+      const int v = tid + kThreads * j;
+      if (v >= have) x[j] = v == have ? last : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+  }
+  if (v0 == 0 && tid == 0) {  // entries before the row
+    if (lead > 0) x[0].x = -INFINITY;
+    if (lead > 1) x[0].y = -INFINITY;
+    if (lead > 2) x[0].z = -INFINITY;
+  }
+
+  // maxima of 16-lane groups, 512 entries each
+  float gm = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kScanVec; ++j) gm = max3(max3(x[j].x, x[j].y, gm), x[j].z, x[j].w);
+  gm = fmax2(gm, dpp<kXor1>(gm));
+  gm = fmax2(gm, dpp<kXor2>(gm));
+  gm = fmax2(gm, dpp<kHalfMirror>(gm));
+  gm = fmax2(gm, dpp<kMirror>(gm));
+  if ((lane & 15) == 0) group_max[tid >> 4] = gm;
+  lds_barrier();
+  // lane i: the maximum over 1, 2, 4, 8, 16 groups around group i % 32, and the
+  // smallest of those for the level; m, the slice's maximum
+  const int cap = slice_cap(words, ns);
+  const float y1 = group_max[lane & 31];
+  const float y2 = fmax2(y1, dpp<kXor1>(y1));
+  const float y4 = fmax2(y2, dpp<kXor2>(y2));
+  const float y8 = fmax2(y4, dpp<kHalfMirror>(y4));
+  const float y16 = fmax2(y8, dpp<kMirror>(y8));
+  const float m = with16(y16, fmax2);
+  // Entries at or above the threshold are listed, the others summed: exp(x - m)
+  // as 2^(x c + off) with c = log2 e and off = -m c, each rounded to float32.
+  const float off = slice_off(m);
+  // the first level whose usual number of listed entries (130, 54, 22, 8, 3) fits
+  int level = cap >= 200 ? 0 : cap >= 100 ? 1 : cap >= 44 ? 2 : cap >= 16 ? 3 : 4;
+  float th;
+  uint32_t before, count, mine;
+  for (;; ++level) {
+    th = level == 0 ? y1 : level == 1 ? y2 : level == 2 ? y4 : level == 3 ? y8 : y16;
+    th = fmin2(th, dpp<kXor1>(th));
+    th = fmin2(th, dpp<kXor2>(th));
+    th = fmin2(th, dpp<kHalfMirror>(th));
+    th = fmin2(th, dpp<kMirror>(th));
+    th = level > 4 ? INFINITY : with16(th, fmin2);
+    // (opaque copies, so that nothing is held in registers across the loop)
+    float th2 = th;
+    uint32_t e0 = 4u * (uint32_t)tid;
+    asm volatile("" : "+v"(th2), "+v"(e0));
+    mine = 0u;
+#pragma unroll
+    for (int j = 0; j < kScanVec; ++j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint64_t bal = __ballot(x[j][i] >= th2);
+        if (bal != 0ull) {  // wave-uniform
+          const uint32_t at = mine + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+          if (x[j][i] >= th2 && at < (uint32_t)kSliceListMax) {
+            list_x[wave][at] = x[j][i];
+            list_i[wave][at] = (uint16_t)(e0 + (uint32_t)(4 * kThreads * j + i));
+          }
+          mine += (uint32_t)__popcll(bal);
+        }
+      }
+    }
+    if (lane == 0) wave_cnt[wave] = mine;
+    lds_barrier();
+    before = count = 0u;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_cnt[w]);
+      before += w < wave ? c : 0u;
+      count += c;
+    }
+    if (count <= (uint32_t)max(cap, 0)) break;  // uniform; always at level 5, which lists nothing
+    lds_barrier();
+  }
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < kScanVec; ++j) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(x[j][i], kLog2e, off));
+      acc[i] += x[j][i] >= th ? 0.f : w;
+    }
+  }
+  double sum = ((double)acc[0] + (double)acc[1]) + ((double)acc[2] + (double)acc[3]);
+  sum = wave_reduce(sum, [](double p, double q) { return p + q; });
+  if (lane == 0) wave_sum[wave] = sum;
+  uint32_t* dst = a.bits + gt.bit_off[b] + (int64_t)row * words + (int64_t)sl * slice_words(words, ns);
+  uint16_t* ids = reinterpret_cast<uint16_t*>(dst + kSliceHead + cap);
+  for (uint32_t i = lane; i < mine; i += 64) {
+    dst[kSliceHead + before + i] = __float_as_uint(list_x[wave][i]);
+    ids[before + i] = list_i[wave][i];
+  }
+  lds_barrier();
+  if (tid == 0) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += wave_sum[w];
+    dst[0] = __float_as_uint(m);
+    dst[1] = level > 4 ? key_of(m) + 1u : key_of(th);
+    dst[2] = __float_as_uint((float)s);
+    dst[3] = count;
+  }
+}
+
+// How far a slice's sum R of n weights e^-d (d: the distance below the slice's
+// maximum m; M is the row's) may be from the exact masses of the same entries,
+// relative to R, beyond which the exact masses only lose their floor.  Entry by
+// entry the errors are at most
+//   1.34e-8 |x|            c against log2 e (|x| <= |m| + d), in the exponent
+//   6e-8 d                 the rounding of the exponent, at most d / log 2 in size
+//   2.4e-7                 the hardware's exponential
+//   5.4e-7                 nine roundings of the float32 sums
+//   6e-8 (d + M - m + 4)   the exact method itself
+// and the mean of d over the weights is at most log(n / R), its value when all
+// of them are equal.  (Entries further than 87 below m have no weight.)
+__device__ __forceinline__ double slice_error(double m, double M, double R, double n) {
+  const double d = fmax(log(n / R), 0.0);
+  return 1.4e-8 * fabs(m) + 1.5e-7 * d + 6e-8 * (M - m) + 1.1e-6;
+}
+
+constexpr int kRowThreads = 256;
+constexpr int kRowWaves = kRowThreads / 64;
+constexpr int kRowBins = 1024;  // bins of the one histogram over the listed keys
+constexpr int kRowBinsPerThread = kRowBins / kRowThreads;
+constexpr int kFew = 64;        // entries of the threshold bin resolved by rank in one wavefront
+constexpr int kLdsWords = 2048; // bitmap words assembled at a time
+
+// Bound: latency (1,344 rows of about 1,000 listed entries take 27 us).  Six
+// 256-thread workgroups per CU (80 registers, 25 KiB of LDS), so that all of
+// those rows are in flight at once; with 33 KiB and four per CU it took 35 us.
+__global__ void __launch_bounds__(kRowThreads, 6)
 golden_row_kernel(GoldenTable gt, GoldenArgs a) {
+  __shared__ uint32_t lkey[kGoldenListMax], lidx[kGoldenListMax];
+  __shared__ __align__(16) uint32_t lbm[kLdsWords];  // the histogram first, then the bitmap
+  __shared__ uint32_t few_key[kFew];
+  __shared__ uint64_t few_q[kFew];
+  __shared__ uint64_t red[4][kRowWaves];
+  __shared__ uint32_t sh_list, sh_few, sh_digit, sh_flag;
+  __shared__ uint64_t sh_above;
+  unsigned long long* hist = reinterpret_cast<unsigned long long*>(lbm);
+  static_assert(kRowBins * 8 <= kLdsWords * 4 && kGoldenListMax <= kLdsWords, "shared areas");
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  {  // the label bitmap and golden-set sizes start at zero (the vote kernel runs after)
+    const int64_t i0 = (int64_t)blockIdx.x * kRowThreads + tid, stride = (int64_t)gridDim.x * kRowThreads;
+    for (int64_t i = i0; i < a.label_words; i += stride) a.label_bits[i] = 0u;
+    if (a.golden_count != nullptr)
+      for (int64_t i = i0; i < (int64_t)gt.batch * a.tau; i += stride) a.golden_count[i] = 0;
+  }
+  const int rows_per_seq = a.tau * a.layers;
+  const int b = blockIdx.x / rows_per_seq, row = blockIdx.x % rows_per_seq;
+  const int n = gt.n[b], words = gt.words[b], ns = gt.slices[b];
+  const float* S = a.logits + gt.logit_off[b] + (int64_t)row * n;
+  uint32_t* bm = a.bits + gt.bit_off[b] + (int64_t)row * words;
+  const uint64_t num = (uint64_t)a.p_num, den = (uint64_t)a.p_den;
+
+  // ---- the listed entries: the whole row (up to kGoldenListMax entries), or
+  // what the scan left of its slices (key 0: none; no finite logit maps to it)
+  constexpr int kPer = kGoldenSlots / kRowThreads;
+  static_assert(kGoldenListMax <= kGoldenSlots, "slots");
+  uint32_t key[kPer], idx[kPer];
+  uint32_t mk = 0u, kth = 0u;  // largest key; entries with keys at or above kth are all listed
+  float hm = 0.f, hsum = 0.f;  // header of slice tid
+  const int sw = ns > 0 ? slice_words(words, ns) : 0, vps = gt.slice_vecs[b];
+  if (ns == 0) {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int e = tid + j * kRowThreads;
+      key[j] = e < n ? key_of(S[e]) : 0u;
+      idx[j] = (uint32_t)e;
+      mk = max(mk, key[j]);
+    }
+    kth = 1u;
+  } else {
+    // slot f is entry f % cap of slice f / cap; the division by multiplication
+    // is exact for f < 2^16
+    const int cap = max(slice_cap(words, ns), 1);
+    const uint32_t inv = (uint32_t)((0xFFFFFFFFull + (uint32_t)cap) / (uint32_t)cap);
+    const int lead = (int)((gt.logit_off[b] + (int64_t)row * n) & 3);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const uint32_t f = (uint32_t)(tid + j * kRowThreads), s = __umulhi(f, inv), i = f - s * (uint32_t)cap;
+      uint32_t v = 0u, id = 0u, c = 0u;
+      if ((int)s < ns) {
+        const uint32_t* src = bm + (int64_t)s * sw;
+        c = src[3];
+        v = src[kSliceHead + i];
+        id = reinterpret_cast<const uint16_t*>(src + kSliceHead + cap)[i];
+      }
+      key[j] = i < c ? key_of(__uint_as_float(v)) : 0u;
+      idx[j] = 4u * s * (uint32_t)vps + id - (uint32_t)lead;
+    }
+    if (tid < ns) {
+      const uint32_t* src = bm + (int64_t)tid * sw;
+      hm = __uint_as_float(src[0]);
+      mk = key_of(hm);
+      kth = src[1];
+      hsum = __uint_as_float(src[2]);
+    }
+    for (int s = tid + kRowThreads; s < ns; s += kRowThreads) {  // rows of over 2^20 entries
+      mk = max(mk, key_of(__uint_as_float(bm[(int64_t)s * sw])));
+      kth = max(kth, bm[(int64_t)s * sw + 1]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kRowBins / kRowThreads; ++i) hist[tid + i * kRowThreads] = 0ull;
+  if (tid == 0) sh_list = sh_few = sh_flag = 0u;
+  mk = wave_reduce(mk, [](uint32_t p, uint32_t q) { return max(p, q); });
+  kth = wave_reduce(kth, [](uint32_t p, uint32_t q) { return max(p, q); });
+  if (lane == 0) red[0][wave] = ((uint64_t)mk << 32) | kth;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kRowWaves; ++w) {
+    mk = max(mk, (uint32_t)(red[0][w] >> 32));
+    kth = max(kth, (uint32_t)red[0][w]);
+  }
+  const float m = logit_of(mk);
+
+  // ---- exact masses of the listed entries; the others' mass lies in an
+  // interval.  Entries at or above kth go to the candidate list; those below
+  // count in the total, but not every entry of their rank is listed.
+  uint64_t all = 0ull, sel = 0ull;
+  uint32_t low = 0xFFFFFFFFu;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    if (__ballot(key[j] != 0u) == 0ull) continue;  // wave-uniform
+    const uint64_t q = key[j] ? mass_of(logit_of(key[j]), m) : 0ull;
+    const bool in = key[j] >= kth && key[j] != 0u;
+    all += q;
+    sel += in ? q : 0ull;
+    const uint64_t bal = __ballot(in);
+    if (bal) {
+      uint32_t at = 0u;
+      if (lane == 0) at = atomicAdd(&sh_list, (uint32_t)__popcll(bal));
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+           __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+      if (in && at < (uint32_t)kGoldenListMax) {
+        lkey[at] = key[j];
+        lidx[at] = idx[j];
+        low = min(low, key[j]);
+      }
+    }
+  }
+  double rest = 0.0, err = 0.0;
+  auto add_slice = [&](float hm_, float hsum_) {
+    if (hsum_ <= 0.f) return;  // (not so for NaN)
+    // the weights' scale is 2^off, not the maximum
+    const double R = (double)hsum_ * exp(-(double)slice_off(hm_) * 0.69314718055994530942 - (double)m);
+    rest += R;
+    err += R * slice_error((double)hm_, (double)m, (double)hsum_, (double)(4 * vps));
+  };
+  if (tid < ns) add_slice(hm, hsum);
+  for (int s = tid + kRowThreads; s < ns; s += kRowThreads)
+    add_slice(__uint_as_float(bm[(int64_t)s * sw]), __uint_as_float(bm[(int64_t)s * sw + 2]));
+  all = wave_reduce(all, [](uint64_t p, uint64_t r) { return p + r; });
+  sel = wave_reduce(sel, [](uint64_t p, uint64_t r) { return p + r; });
+  low = wave_reduce(low, [](uint32_t p, uint32_t r) { return min(p, r); });
+  // (the slices' headers sit in the first ns threads)
+  if (64 * wave < ns) {
+    rest = wave_reduce(rest, [](double p, double r) { return p + r; });
+    err = wave_reduce(err, [](double p, double r) { return p + r; });
+  }
+  __syncthreads();  // red[0]
+  if (lane == 0) {
+    red[0][wave] = all;
+    red[1][wave] = sel;
+    red[2][wave] = (uint64_t)__double_as_longlong(rest);
+    red[3][wave] = (uint64_t)__double_as_longlong(err);
+    atomicMax(&sh_flag, ~low);
+  }
+  __syncthreads();
+  all = sel = 0ull;
+  rest = err = 0.0;
+#pragma unroll
+  for (int w = 0; w < kRowWaves; ++w) {
+    all += red[0][w];
+    sel += red[1][w];
+    rest += __longlong_as_double((long long)red[2][w]);
+    err += __longlong_as_double((long long)red[3][w]);
+  }
+  low = ~sh_flag;  // the smallest candidate key
+  const int nl = (int)sh_list;
+  u128 need_lo, need_hi;
+  bool fast = nl > 0 && nl <= kGoldenListMax;
+  if (ns == 0) {
+    need_lo = need_hi = mul64(all, num);
+  } else {
+    // (and one unit per entry for the floor of the masses)
+    constexpr double kUnit = 1099511627776.0;  // 2^40
+    const double slack = err * kUnit + 8.0;
+    const double r = rest * kUnit;
+    fast = fast && r + slack < 4.0e18;  // not so for a sum past the range (NaN included)
+    const uint64_t rhi = fast ? (uint64_t)(r + slack) + 1ull : 0ull;
+    const double least = r - slack - (double)n;
+    const uint64_t rlo = fast && least > 0.0 ? (uint64_t)least : 0ull;
+    need_lo = mul64(all + rlo, num);
+    need_hi = mul64(all + rhi, num);
+    fast = fast && ge128(mul64(sel, den), need_hi);
+  }
+
+  // ---- the bin of the candidates' keys where the mass reaches p, then the
+  // entries in it by rank.  Every decision below is uniform.
+  const uint32_t span = mk - low;
+  const int shift = span >> 10 ? 32 - __builtin_clz(span) - 10 : 0;
+  uint32_t T = 0u, ties = 0u, r = 0u;
+  while (fast) {  // once: a break leaves the row open
+    for (int i = tid; i < nl; i += kRowThreads)
+      atomicAdd(&hist[(lkey[i] - low) >> shift], (unsigned long long)mass_of(logit_of(lkey[i]), m));
+    __syncthreads();
+    // descending: thread t owns the bins below 1023 - kRowBinsPerThread t
+    uint64_t mine[kRowBinsPerThread], mine_sum = 0ull;
+#pragma unroll
+    for (int j = 0; j < kRowBinsPerThread; ++j) {
+      mine[j] = hist[kRowBins - 1 - kRowBinsPerThread * tid - j];
+      mine_sum += mine[j];
+    }
+    uint64_t incl = mine_sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    if (lane == 63) red[0][wave] = incl;
+    if (tid == 0) sh_flag = 0u;
+    __syncthreads();
+    uint64_t ex = incl - mine_sum;
+#pragma unroll
+    for (int w = 0; w < kRowWaves; ++w) ex += w < wave ? red[0][w] : 0ull;
+#pragma unroll
+    for (int j = 0; j < kRowBinsPerThread; ++j) {
+      if (!ge128(mul64(ex, den), need_hi) && ge128(mul64(ex + mine[j], den), need_hi)) {
+        sh_digit = (uint32_t)(kRowBins - 1 - kRowBinsPerThread * tid - j);
+        sh_above = ex;
+        sh_flag = 1u;
+      }
+      ex += mine[j];
+    }
+    __syncthreads();
+    if (sh_flag == 0u) {  // no crossing (a logit that is not finite)
+      fast = false;
+      break;
+    }
+    const uint32_t digit = sh_digit;
+    for (int i = tid; i < nl; i += kRowThreads) {
+      if (((lkey[i] - low) >> shift) == digit) {
+        const uint32_t at = atomicAdd(&sh_few, 1u);
+        if (at < (uint32_t)kFew) {
+          few_key[at] = lkey[i];
+          few_q[at] = mass_of(logit_of(lkey[i]), m);
+        }
+      }
+    }
+    __syncthreads();
+    const int nf = (int)sh_few;
+    if (nf > kFew) {  // many equal or close logits at the boundary
+      fast = false;
+      break;
+    }
+    // lane i: entry i of the bin, the mass above it, and how many equal it
+    const uint32_t fk = lane < nf ? few_key[lane] : 0u;
+    uint64_t above = sh_above;
+    ties = 0u;
+    for (int i = 0; i < nf; ++i) {
+      above += few_key[i] > fk ? few_q[i] : 0ull;
+      ties += few_key[i] == fk ? 1u : 0u;
+    }
+    const uint64_t qT = lane < nf ? few_q[lane] : 0ull;
+    const uint64_t hit = __ballot(lane < nf && !ge128(mul64(above, den), need_hi) &&
+                                  ge128(mul64(above + (uint64_t)ties * qT, den), need_hi));
+    if (hit == 0ull) {
+      fast = false;
+      break;
+    }
+    // the fewest entries equal to T that reach the mass (1 .. ties)
+    uint32_t lo = 1, hi = ties;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) / 2;
+      if (ge128(mul64(above + (uint64_t)mid * qT, den), need_hi)) hi = mid;
+      else lo = mid + 1;
+    }
+    // settled when one entry less stays short of p at the other end too
+    const bool sure = !ge128(mul64(above + (uint64_t)(lo - 1u) * qT, den), need_lo);
+    const int first = __builtin_ctzll(hit);
+    T = (uint32_t)__builtin_amdgcn_readlane((int)fk, first);
+    r = (uint32_t)__builtin_amdgcn_readlane((int)lo, first);
+    ties = (uint32_t)__builtin_amdgcn_readlane((int)ties, first);
+    // (otherwise the boundary falls inside the interval: about one row in 10,000)
+    fast = __builtin_amdgcn_readlane((int)sure, first) != 0;
+    break;
+  }
+  if (tid == 0) a.row_flags[blockIdx.x] = fast ? 0u : 1u;
+  if (!fast) return;  // golden_general_kernel decides this row
+
+  // ---- members: candidates above T, and the r entries equal to T with the lowest ids
+  const bool some = r != ties;
+  for (int w0 = 0; w0 < words; w0 += kLdsWords) {
+    const int nw = min(words - w0, kLdsWords);
+    __syncthreads();
+    for (int w = tid; w < nw; w += kRowThreads) lbm[w] = 0u;
+    __syncthreads();
+    for (int i = tid; i < nl; i += kRowThreads) {
+      const uint32_t k = lkey[i], e = lidx[i];
+      bool in = k >= T;
+      if (some && k == T) {
+        uint32_t rank = 0u;
+        for (int j = 0; j < nl; ++j) rank += lkey[j] == T && lidx[j] < e ? 1u : 0u;
+        in = rank < r;
+      }
+      const int w = (int)(e >> 5) - w0;
+      if (in && w >= 0 && w < nw) atomicOr(&lbm[w], 1u << (e & 31u));
+    }
+    __syncthreads();
+    for (int w = tid; w < nw; w += kRowThreads) bm[w0 + w] = lbm[w];
+  }
+  if (a.nucleus_size != nullptr) {
+    uint32_t n_in = 0u;
+    for (int i = tid; i < nl; i += kRowThreads) n_in += lkey[i] > T ? 1u : 0u;
+    n_in = wave_reduce(n_in, [](uint32_t p, uint32_t s) { return p + s; });
+    if (lane == 0) red[1][wave] = n_in;
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t total = r;
+#pragma unroll
+      for (int w = 0; w < kRowWaves; ++w) total += (uint32_t)red[1][w];
+      a.nucleus_size[(int64_t)b * rows_per_seq + row] = (int32_t)total;
+    }
+  }
+}
+
+// The rows that the row kernel left open: flat ones, whose set reaches below
+// the listed entries, and those with more than kFew entries at the boundary.
+__global__ void __launch_bounds__(kThreads)
+golden_general_kernel(GoldenTable gt, GoldenArgs a) {
+  if (a.row_flags[blockIdx.x] == 0u) return;  // the whole workgroup
   __shared__ unsigned long long hist[kBins];
   __shared__ uint32_t sub_cnt[kSubBins];
   __shared__ uint32_t cand_key[kCand];
   __shared__ uint32_t cand_idx[kCand];
   __shared__ uint64_t wave_tot[kWaves];
-  __shared__ float wave_max[kWaves];
+  __shared__ uint32_t wave_mk[kWaves];
   __shared__ uint32_t sh_cnt, sh_digit;
   __shared__ uint64_t sh_above;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (blockIdx.x == 0) {  // the label bitmap and golden-set sizes start at zero (the vote kernel runs after)
-    for (int64_t i = tid; i < a.label_words; i += kThreads) a.label_bits[i] = 0u;
-    if (a.golden_count != nullptr)
-      for (int64_t i = tid; i < (int64_t)gt.batch * a.tau; i += kThreads) a.golden_count[i] = 0;
-  }
   const int rows_per_seq = a.tau * a.layers;
   const int b = blockIdx.x / rows_per_seq, row = blockIdx.x % rows_per_seq;
-  const int n = gt.n[b], words = gt.words[b];
+  const int n = gt.n[b], words = gt.words[b], ns = gt.slices[b];
   const float* S = a.logits + gt.logit_off[b] + (int64_t)row * n;
   uint32_t* bm = a.bits + gt.bit_off[b] + (int64_t)row * words;
+
+  // the row's maximum: the largest of its slices', or of the (short) row itself
+  uint32_t mk = 0u;
+  if (ns == 0)
+    for (int e = tid; e < n; e += kThreads) mk = max(mk, key_of(S[e]));
+  else
+    for (int sl = tid; sl < ns; sl += kThreads)
+      mk = max(mk, key_of(__uint_as_float(bm[(int64_t)sl * slice_words(words, ns)])));
+  mk = wave_reduce(mk, [](uint32_t p, uint32_t q) { return max(p, q); });
+  if (lane == 0) wave_mk[wave] = mk;
+  for (int i = tid; i < kBins; i += kThreads) hist[i] = 0ull;
+  if (tid == 0) sh_cnt = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) mk = max(mk, wave_mk[w]);
+  const float m = logit_of(mk);
 
   // entry of group u of round base for this lane: 64 consecutive entries per
   // wavefront load, kUnroll consecutive groups per wavefront
   auto entry = [&](int base, int u) { return base + (wave * kUnroll + u) * 64 + lane; };
   constexpr int kRound = kThreads * kUnroll;
 
-  // ---- pass 1: maximum
-  float mx = -INFINITY;
-  for (int base = 0; base < n; base += kRound) {
-    float v[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int e = entry(base, u);
-      v[u] = e < n ? S[e] : -INFINITY;
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) mx = fmaxf(mx, v[u]);
-  }
-  mx = wave_reduce(mx, [](float x, float y) { return fmaxf(x, y); });
-  for (int i = tid; i < kBins; i += kThreads) hist[i] = 0ull;
-  if (lane == 0) wave_max[wave] = mx;
-  if (tid == 0) sh_cnt = 0u;
-  __syncthreads();
-  float m = wave_max[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) m = fmaxf(m, wave_max[w]);
-
-  // ---- pass 2: mass histogram by the top 12 bits of the order key
+  // ---- first pass: mass histogram by the top 12 bits of the order key
   for (int base = 0; base < n; base += kRound) {
     float v[kUnroll];
 #pragma unroll
@@ -209,7 +765,7 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
   const uint32_t bstar = sh_digit;
   uint64_t above = sh_above;  // mass of every key above the current prefix
 
-  // ---- pass 3: bitmap of the bins above bstar, entries of bstar to LDS
+  // ---- second pass: bitmap of the bins above bstar, entries of bstar to LDS
   uint32_t n_in = 0;
   for (int base = 0; base < n; base += kRound) {
     float v[kUnroll];
@@ -355,76 +911,101 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
 
 // Bit-sliced vote counters: c[k] holds bit k of the count of each of 32 entries.
 constexpr int kCountBits = 7;  // counts up to 127 >= LSA_MAX_GOLDEN_LAYERS
+constexpr int kVoteSteps = 2;  // steps per thread: one OR into the label bitmap serves both (11.9 us with one
+                               // step, 9.2 with two, 11.0 with four for 22 MB of bitmaps; too few wavefronts past two)
+constexpr int kVoteBatch = 24; // layers' words in flight at once
 
 __global__ void __launch_bounds__(256)
 golden_vote_kernel(GoldenTable gt, GoldenArgs a, uint32_t* __restrict__ label_bits, int32_t* golden_count) {
-  const int b = blockIdx.z, i = blockIdx.y;
+  __shared__ uint32_t cnt_sh[kVoteSteps];
+  const int b = blockIdx.z, i0 = blockIdx.y * kVoteSteps;
   const int w = blockIdx.x * 256 + threadIdx.x;
   const int words = gt.words[b];
-  uint32_t A = 0u;
-  if (w < words) {
-    uint32_t c[kCountBits] = {};
-    const uint32_t* src = a.bits + gt.bit_off[b] + (int64_t)i * a.layers * words + w;
-    // the layers' words eight at a time, every load of a batch in flight at once
-    for (int l0 = 0; l0 < a.layers; l0 += 8) {
-      uint32_t x[8];
+  if (blockIdx.x * 256 >= words) return;  // the whole workgroup
+  if (threadIdx.x < kVoteSteps) cnt_sh[threadIdx.x] = 0u;
+  __syncthreads();
+  uint32_t label = 0u;
+  for (int i = i0; i < min(i0 + kVoteSteps, a.tau); ++i) {
+    uint32_t A = 0u;
+    if (w < words) {
+      uint32_t c[kCountBits] = {};
+      const uint32_t* src = a.bits + gt.bit_off[b] + (int64_t)i * a.layers * words + w;
+      for (int l0 = 0; l0 < a.layers; l0 += kVoteBatch) {
+        uint32_t x[kVoteBatch];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = l0 + j < a.layers ? src[(int64_t)(l0 + j) * words] : 0u;
+        for (int j = 0; j < kVoteBatch; ++j) x[j] = l0 + j < a.layers ? src[(int64_t)(l0 + j) * words] : 0u;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        uint32_t carry = x[j];
+        for (int j = 0; j < kVoteBatch; ++j) {
+          uint32_t carry = x[j];
 #pragma unroll
-        for (int k = 0; k < kCountBits; ++k) {
-          const uint32_t t = c[k] & carry;
-          c[k] ^= carry;
-          carry = t;
+          for (int k = 0; k < kCountBits; ++k) {
+            const uint32_t t = c[k] & carry;
+            c[k] ^= carry;
+            carry = t;
+          }
         }
       }
-    }
-    // count >= theta, bit-sliced, from the most significant bit down
-    uint32_t gt_ = 0u, eq = 0xFFFFFFFFu;
+      // count >= theta, bit-sliced, from the most significant bit down
+      uint32_t gt_ = 0u, eq = 0xFFFFFFFFu;
 #pragma unroll
-    for (int k = kCountBits - 1; k >= 0; --k) {
-      if ((a.theta >> k) & 1) {
-        eq &= c[k];
-      } else {
-        gt_ |= eq & c[k];
-        eq &= ~c[k];
+      for (int k = kCountBits - 1; k >= 0; --k) {
+        if ((a.theta >> k) & 1) {
+          eq &= c[k];
+        } else {
+          gt_ |= eq & c[k];
+          eq &= ~c[k];
+        }
       }
+      A = gt_ | eq;
     }
-    A = gt_ | eq;
-    if (A) atomicOr(&label_bits[gt.label_word_off[b] + w], A);
+    label |= A;
+    if (golden_count != nullptr && __ballot(A != 0u) != 0ull) {
+      uint32_t cnt = (uint32_t)__popc(A);
+      cnt = wave_reduce(cnt, [](uint32_t x, uint32_t y) { return x + y; });
+      if ((threadIdx.x & 63) == 0) atomicAdd(&cnt_sh[i - i0], cnt);
+    }
   }
+  if (label) atomicOr(&label_bits[gt.label_word_off[b] + w], label);
   if (golden_count != nullptr) {
-    uint32_t cnt = (uint32_t)__popc(A);
-    cnt = wave_reduce(cnt, [](uint32_t x, uint32_t y) { return x + y; });
-    if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(&golden_count[b * a.tau + i], (int32_t)cnt);
+    __syncthreads();
+    if (threadIdx.x < kVoteSteps && cnt_sh[threadIdx.x] != 0u)
+      atomicAdd(&golden_count[b * a.tau + i0 + threadIdx.x], (int32_t)cnt_sh[threadIdx.x]);
   }
 }
 
+// Rounds of 4 consecutive words per thread, held in registers between the
+// count and the emission.
 __global__ void __launch_bounds__(kThreads)
 golden_compact_kernel(GoldenTable gt, const uint32_t* __restrict__ label_bits, int32_t* labels,
                       int32_t* label_count) {
+  constexpr int kPer = 8;
   __shared__ uint64_t wave_tot[kWaves];
   const int b = blockIdx.x, tid = threadIdx.x;
   const int words = gt.words[b];
   const uint32_t* src = label_bits + gt.label_word_off[b];
-  const int seg = (words + kThreads - 1) / kThreads;
-  const int w0 = min(tid * seg, words), w1 = min(w0 + seg, words);
-  uint64_t cnt = 0;
-  for (int w = w0; w < w1; ++w) cnt += __popc(src[w]);
-  uint64_t total;
-  uint64_t pos = block_scan_u64(cnt, wave_tot, &total);
   int32_t* out = labels + gt.entry_off[b];
-  for (int w = w0; w < w1; ++w) {
-    uint32_t x = src[w];
-    while (x) {
-      const int bit = __builtin_ctz(x);
-      x &= x - 1u;
-      out[pos++] = 32 * w + bit;
+  uint64_t base = 0;
+  for (int r0 = 0; r0 < words; r0 += kThreads * kPer) {
+    const int w0 = r0 + tid * kPer;
+    uint32_t x[kPer];
+    uint64_t cnt = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      x[j] = w0 + j < words ? src[w0 + j] : 0u;
+      cnt += (uint64_t)__popc(x[j]);
     }
+    uint64_t total;
+    uint64_t pos = base + block_scan_u64(cnt, wave_tot, &total);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      while (x[j]) {
+        out[pos++] = 32 * (w0 + j) + __builtin_ctz(x[j]);
+        x[j] &= x[j] - 1u;
+      }
+    }
+    base += total;
   }
-  if (tid == 0) label_count[b] = (int32_t)total;
+  if (tid == 0) label_count[b] = (int32_t)base;
 }
 
 }  // namespace
@@ -435,10 +1016,17 @@ hipError_t launch_golden(const GoldenTable& gt, const GoldenArgs& a, uint32_t* l
   ra.label_bits = label_bits;
   ra.label_words = label_words;
   ra.golden_count = golden_count;
-  hipLaunchKernelGGL(golden_row_kernel, dim3((unsigned)(gt.batch * a.tau * a.layers)), dim3(kThreads), 0, s, gt, ra);
+  if (gt.scan_off[gt.batch] > 0)
+    hipLaunchKernelGGL(golden_scan_kernel, dim3((unsigned)gt.scan_off[gt.batch]), dim3(kThreads), 0, s, gt, ra);
+  hipLaunchKernelGGL(golden_row_kernel, dim3((unsigned)(gt.batch * a.tau * a.layers)), dim3(kRowThreads), 0, s, gt,
+                     ra);
+  hipLaunchKernelGGL(golden_general_kernel, dim3((unsigned)(gt.batch * a.tau * a.layers)), dim3(kThreads), 0, s, gt,
+                     ra);
   int max_words = 0;
   for (int b = 0; b < gt.batch; ++b) max_words = std::max(max_words, gt.words[b]);
-  hipLaunchKernelGGL(golden_vote_kernel, dim3((unsigned)((max_words + 255) / 256), (unsigned)a.tau, (unsigned)gt.batch),
+  hipLaunchKernelGGL(golden_vote_kernel,
+                     dim3((unsigned)((max_words + 255) / 256), (unsigned)((a.tau + kVoteSteps - 1) / kVoteSteps),
+                          (unsigned)gt.batch),
                      dim3(256), 0, s, gt, a, label_bits, golden_count);
   hipLaunchKernelGGL(golden_compact_kernel, dim3((unsigned)gt.batch), dim3(kThreads), 0, s, gt,
                      (const uint32_t*)label_bits, labels, label_count);

@@ -435,7 +435,7 @@ struct GoldenPlan {
   GoldenTable t;
   int64_t row_words = 0;    // words of all row bitmaps
   int64_t label_words = 0;  // words of the label bitmaps
-  size_t off_bits = 0, off_labels = 0, ws_total = 0;
+  size_t off_bits = 0, off_labels = 0, off_flags = 0, ws_total = 0;
 };
 
 lsa_status make_golden_plan(const lsa_golden* g, GoldenPlan* gp) {
@@ -456,7 +456,7 @@ lsa_status make_golden_plan(const lsa_golden* g, GoldenPlan* gp) {
   memset(&t, 0, sizeof t);
   t.batch = g->batch;
   const int64_t rows = (int64_t)g->n_steps * g->n_layers;
-  int64_t entries = 0, bits = 0, labels = 0;
+  int64_t entries = 0, bits = 0, labels = 0, scans = 0;
   for (int b = 0; b < g->batch; ++b) {
     const int64_t n = g->n_entries[b];
     if (n < 1 || n > LSA_MAX_GOLDEN_ENTRIES)
@@ -468,15 +468,27 @@ lsa_status make_golden_plan(const lsa_golden* g, GoldenPlan* gp) {
     t.logit_off[b] = rows * entries;
     t.bit_off[b] = bits;
     t.label_word_off[b] = labels;
+    // rows longer than the row kernel holds are scanned in slices of equal
+    // length; a row that does not start on a float4 spans one float4 more
+    t.scan_off[b] = scans;
+    if (n > kGoldenListMax) {
+      const bool aligned = n % 4 == 0 && t.logit_off[b] % 4 == 0;
+      const int64_t vecs = aligned ? n / 4 : (n + 6) / 4;
+      t.slices[b] = (int32_t)((vecs + kGoldenSliceVecs - 1) / kGoldenSliceVecs);
+      t.slice_vecs[b] = (int32_t)((vecs + t.slices[b] - 1) / t.slices[b]);
+      scans += rows * t.slices[b];
+    }
     entries += n;
     bits += rows * t.words[b];
     labels += t.words[b];
   }
+  t.scan_off[g->batch] = scans;
   gp->row_words = bits;
   gp->label_words = labels;
   gp->off_bits = 0;
   gp->off_labels = align_up((size_t)bits * 4);
-  gp->ws_total = align_up(gp->off_labels + (size_t)labels * 4);
+  gp->off_flags = align_up(gp->off_labels + (size_t)labels * 4);
+  gp->ws_total = align_up(gp->off_flags + (size_t)(g->batch * rows) * 4);
   return LSA_OK;
 }
 
@@ -1157,10 +1169,13 @@ lsa_status lsa_golden_labels(const lsa_golden* g, const float* logits, int32_t* 
   if (ws_bytes < G.ws_total)
     return fail(LSA_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, G.ws_total);
   if (ws == nullptr || !aligned16(ws)) return fail(LSA_ERR_WORKSPACE, "workspace is NULL or not 16-byte aligned");
+  if (G.t.scan_off[g->batch] > INT32_MAX)  // (logits past any GPU's memory)
+    return fail(LSA_ERR_UNSUPPORTED, "too many row slices for one launch");
   GoldenArgs a;
   a.logits = logits;
   a.bits = reinterpret_cast<uint32_t*>(at(ws, G.off_bits));
   a.nucleus_size = nucleus_size;
+  a.row_flags = reinterpret_cast<uint32_t*>(at(ws, G.off_flags));
   a.p_num = g->p_num;
   a.p_den = g->p_den;
   a.tau = g->n_steps;

@@ -269,6 +269,11 @@ hipError_t launch_tier_fetch(const SeqTable& t, const TierFetchArgs& a, int32_t 
 hipError_t launch_tier_reset(int32_t* owner, int64_t n, hipStream_t s);
 
 // Golden-label pipeline: per-sequence geometry (by value) and launch arguments.
+// The row kernel holds up to kGoldenListMax entries of a row; a longer row is
+// scanned first, in slices of up to kGoldenSliceVecs float4s (16,384 entries),
+// which leave their largest entries to it.
+constexpr int kGoldenListMax = 2048;
+constexpr int kGoldenSliceVecs = 4096;
 struct GoldenTable {
   int32_t batch;
   int32_t n[LSA_MAX_BATCH];                // entries n_b
@@ -277,11 +282,15 @@ struct GoldenTable {
   int64_t logit_off[LSA_MAX_BATCH];        // first logit of sequence b, tau * L * entry_off[b]
   int64_t bit_off[LSA_MAX_BATCH];          // first word of sequence b's row bitmaps
   int64_t label_word_off[LSA_MAX_BATCH];   // first word of sequence b's label bitmap
+  int32_t slices[LSA_MAX_BATCH];           // slices a row is scanned in, 0: the row kernel reads the whole row
+  int32_t slice_vecs[LSA_MAX_BATCH];       // float4s per slice
+  int64_t scan_off[LSA_MAX_BATCH + 1];     // first scan workgroup of sequence b, one per (row, slice)
 };
 struct GoldenArgs {
   const float* logits;
   uint32_t* bits;          // [sum_b tau * L * words_b] top-p membership per row
   int32_t* nucleus_size;   // nullable [B][tau][L]
+  uint32_t* row_flags;     // [B tau L] rows that the row kernel leaves to the general one
   uint32_t* label_bits = nullptr;    // [label_words] zeroed by the row kernel's first workgroup
   int64_t label_words = 0;
   int32_t* golden_count = nullptr;   // nullable [B][tau], zeroed likewise
