@@ -23,14 +23,14 @@
 //   the listed entries (or the whole row up to 2,048 entries).  Their masses
 //   are exact; the mass of all other entries lies in an interval that bounds
 //   every rounding of the approximate sum.  A 1024-bin LDS histogram of the
-//   listed masses finds the bin where the cumulative mass reaches p, and the
-//   few entries in it are ranked by one wavefront: the threshold key T and the
+//   listed masses finds the bin where the cumulative mass reaches p (once more
+//   inside a bin of many entries), whose entries are ranked directly: the threshold key T and the
 //   number of entries equal to T that the set needs.  When both ends of the
 //   interval give the same answer it is the exact one, and the row's bitmap is
 //   assembled in LDS.
 // golden_general_kernel -- the rows left open (flat ones, whose set reaches
-//   below the listed entries; many equal logits at the boundary; a boundary
-//   inside the interval) are read twice more: a 4096-bin LDS histogram of the
+//   below the listed entries, or a boundary inside the interval) are read twice
+//   more: a 4096-bin LDS histogram of the
 //   exact masses by the top 12 bits of each logit's order key, whose descending
 //   scan finds the bin where the cumulative mass reaches p, then the bitmap of
 //   the bins above it (wavefront ballots) with the entries of that bin staged
@@ -371,6 +371,11 @@ __device__ __forceinline__ double slice_error(double m, double M, double R, doub
   return 1.4e-8 * fabs(m) + 1.5e-7 * d + 6e-8 * (M - m) + 1.1e-6;
 }
 
+// Mark of a scanned row that the row kernel leaves open, in a word of its
+// bitmap that holds a list entry of the first slice until then.
+constexpr int kOpenWord = kSliceHead;
+constexpr uint32_t kOpenRow = 0x9E3779B9u;
+
 constexpr int kRowThreads = 256;
 constexpr int kRowWaves = kRowThreads / 64;
 constexpr int kRowBins = 1024;  // bins of the one histogram over the listed keys
@@ -553,13 +558,17 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
   }
 
   // ---- the bin of the candidates' keys where the mass reaches p, then the
-  // entries in it by rank.  Every decision below is uniform.
-  const uint32_t span = mk - low;
-  const int shift = span >> 10 ? 32 - __builtin_clz(span) - 10 : 0;
+  // entries in it by rank (or its 1,024 sub-bins, when it holds more than
+  // kFew).  Every decision below is uniform.
   uint32_t T = 0u, ties = 0u, r = 0u;
-  while (fast) {  // once: a break leaves the row open
+  uint32_t base = low, top = mk;  // the range of keys the threshold lies in
+  uint64_t over = 0ull;           // mass of the candidates above it
+  while (fast) {
+    const uint32_t span = top - base;
+    const int shift = span >> 10 ? 32 - __builtin_clz(span) - 10 : 0;
     for (int i = tid; i < nl; i += kRowThreads)
-      atomicAdd(&hist[(lkey[i] - low) >> shift], (unsigned long long)mass_of(logit_of(lkey[i]), m));
+      if (lkey[i] >= base && lkey[i] <= top)
+        atomicAdd(&hist[(lkey[i] - base) >> shift], (unsigned long long)mass_of(logit_of(lkey[i]), m));
     __syncthreads();
     // descending: thread t owns the bins below 1023 - kRowBinsPerThread t
     uint64_t mine[kRowBinsPerThread], mine_sum = 0ull;
@@ -577,7 +586,7 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
     if (lane == 63) red[0][wave] = incl;
     if (tid == 0) sh_flag = 0u;
     __syncthreads();
-    uint64_t ex = incl - mine_sum;
+    uint64_t ex = over + incl - mine_sum;
 #pragma unroll
     for (int w = 0; w < kRowWaves; ++w) ex += w < wave ? red[0][w] : 0ull;
 #pragma unroll
@@ -594,9 +603,11 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
       fast = false;
       break;
     }
-    const uint32_t digit = sh_digit;
+    base += sh_digit << shift;
+    top = base + ((1u << shift) - 1u);
+    over = sh_above;
     for (int i = tid; i < nl; i += kRowThreads) {
-      if (((lkey[i] - low) >> shift) == digit) {
+      if (lkey[i] >= base && lkey[i] <= top) {
         const uint32_t at = atomicAdd(&sh_few, 1u);
         if (at < (uint32_t)kFew) {
           few_key[at] = lkey[i];
@@ -606,20 +617,26 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
     }
     __syncthreads();
     const int nf = (int)sh_few;
-    if (nf > kFew) {  // many equal or close logits at the boundary
-      fast = false;
-      break;
+    if (nf > kFew && shift > 0) {
+      __syncthreads();  // sh_few and the histogram start again
+      if (tid == 0) sh_few = 0u;
+#pragma unroll
+      for (int i = 0; i < kRowBins / kRowThreads; ++i) hist[tid + i * kRowThreads] = 0ull;
+      __syncthreads();
+      continue;
     }
-    // lane i: entry i of the bin, the mass above it, and how many equal it
-    const uint32_t fk = lane < nf ? few_key[lane] : 0u;
-    uint64_t above = sh_above;
-    ties = 0u;
-    for (int i = 0; i < nf; ++i) {
+    // lane i: entry i of the bin, the mass above it, and how many equal it (a
+    // bin of one key: every lane stands for that key)
+    const bool one = nf > kFew;
+    const uint32_t fk = one ? base : lane < nf ? few_key[lane] : 0u;
+    const uint64_t qT = one ? few_q[0] : lane < nf ? few_q[lane] : 0ull;
+    uint64_t above = over;
+    ties = one ? (uint32_t)nf : 0u;
+    for (int i = 0; i < nf && !one; ++i) {
       above += few_key[i] > fk ? few_q[i] : 0ull;
       ties += few_key[i] == fk ? 1u : 0u;
     }
-    const uint64_t qT = lane < nf ? few_q[lane] : 0ull;
-    const uint64_t hit = __ballot(lane < nf && !ge128(mul64(above, den), need_hi) &&
+    const uint64_t hit = __ballot((one || lane < nf) && !ge128(mul64(above, den), need_hi) &&
                                   ge128(mul64(above + (uint64_t)ties * qT, den), need_hi));
     if (hit == 0ull) {
       fast = false;
@@ -642,8 +659,10 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
     fast = __builtin_amdgcn_readlane((int)sure, first) != 0;
     break;
   }
-  if (tid == 0) a.row_flags[blockIdx.x] = fast ? 0u : 1u;
-  if (!fast) return;  // golden_general_kernel decides this row
+  if (!fast && ns > 0) {  // golden_general_kernel decides this row
+    if (tid == 0) bm[kOpenWord] = kOpenRow;
+    return;
+  }
 
   // ---- members: candidates above T, and the r entries equal to T with the lowest ids
   const bool some = r != ties;
@@ -664,6 +683,12 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
       if (in && w >= 0 && w < nw) atomicOr(&lbm[w], 1u << (e & 31u));
     }
     __syncthreads();
+    // (a bitmap that happens to hold the mark of an open row there is left to
+    // the general path, whose result is the same)
+    if (w0 == 0 && ns > 0 && lbm[kOpenWord] == kOpenRow) {
+      if (tid == 0) bm[kOpenWord] = kOpenRow;
+      return;
+    }
     for (int w = tid; w < nw; w += kRowThreads) bm[w0 + w] = lbm[w];
   }
   if (a.nucleus_size != nullptr) {
@@ -681,11 +706,9 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
   }
 }
 
-// The rows that the row kernel left open: flat ones, whose set reaches below
-// the listed entries, and those with more than kFew entries at the boundary.
+// The scanned rows that the row kernel left open.
 __global__ void __launch_bounds__(kThreads)
 golden_general_kernel(GoldenTable gt, GoldenArgs a) {
-  if (a.row_flags[blockIdx.x] == 0u) return;  // the whole workgroup
   __shared__ unsigned long long hist[kBins];
   __shared__ uint32_t sub_cnt[kSubBins];
   __shared__ uint32_t cand_key[kCand];
@@ -701,14 +724,12 @@ golden_general_kernel(GoldenTable gt, GoldenArgs a) {
   const int n = gt.n[b], words = gt.words[b], ns = gt.slices[b];
   const float* S = a.logits + gt.logit_off[b] + (int64_t)row * n;
   uint32_t* bm = a.bits + gt.bit_off[b] + (int64_t)row * words;
+  if (ns == 0 || bm[kOpenWord] != kOpenRow) return;  // the whole workgroup
 
-  // the row's maximum: the largest of its slices', or of the (short) row itself
+  // the row's maximum, the largest of its slices'
   uint32_t mk = 0u;
-  if (ns == 0)
-    for (int e = tid; e < n; e += kThreads) mk = max(mk, key_of(S[e]));
-  else
-    for (int sl = tid; sl < ns; sl += kThreads)
-      mk = max(mk, key_of(__uint_as_float(bm[(int64_t)sl * slice_words(words, ns)])));
+  for (int sl = tid; sl < ns; sl += kThreads)
+    mk = max(mk, key_of(__uint_as_float(bm[(int64_t)sl * slice_words(words, ns)])));
   mk = wave_reduce(mk, [](uint32_t p, uint32_t q) { return max(p, q); });
   if (lane == 0) wave_mk[wave] = mk;
   for (int i = tid; i < kBins; i += kThreads) hist[i] = 0ull;

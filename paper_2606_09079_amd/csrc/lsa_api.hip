@@ -435,7 +435,7 @@ struct GoldenPlan {
   GoldenTable t;
   int64_t row_words = 0;    // words of all row bitmaps
   int64_t label_words = 0;  // words of the label bitmaps
-  size_t off_bits = 0, off_labels = 0, off_flags = 0, ws_total = 0;
+  size_t off_bits = 0, off_labels = 0, ws_total = 0;
 };
 
 lsa_status make_golden_plan(const lsa_golden* g, GoldenPlan* gp) {
@@ -487,8 +487,7 @@ lsa_status make_golden_plan(const lsa_golden* g, GoldenPlan* gp) {
   gp->label_words = labels;
   gp->off_bits = 0;
   gp->off_labels = align_up((size_t)bits * 4);
-  gp->off_flags = align_up(gp->off_labels + (size_t)labels * 4);
-  gp->ws_total = align_up(gp->off_flags + (size_t)(g->batch * rows) * 4);
+  gp->ws_total = align_up(gp->off_labels + (size_t)labels * 4);
   return LSA_OK;
 }
 
@@ -1175,7 +1174,6 @@ lsa_status lsa_golden_labels(const lsa_golden* g, const float* logits, int32_t* 
   a.logits = logits;
   a.bits = reinterpret_cast<uint32_t*>(at(ws, G.off_bits));
   a.nucleus_size = nucleus_size;
-  a.row_flags = reinterpret_cast<uint32_t*>(at(ws, G.off_flags));
   a.p_num = g->p_num;
   a.p_den = g->p_den;
   a.tau = g->n_steps;

@@ -290,7 +290,6 @@ struct GoldenArgs {
   const float* logits;
   uint32_t* bits;          // [sum_b tau * L * words_b] top-p membership per row
   int32_t* nucleus_size;   // nullable [B][tau][L]
-  uint32_t* row_flags;     // [B tau L] rows that the row kernel leaves to the general one
   uint32_t* label_bits = nullptr;    // [label_words] zeroed by the row kernel's first workgroup
   int64_t label_words = 0;
   int32_t* golden_count = nullptr;   // nullable [B][tau], zeroed likewise
