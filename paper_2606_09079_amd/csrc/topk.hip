@@ -21,6 +21,8 @@
 //     candidates, with no barriers;
 //   - the kept set is built as bitmaps straight from wavefront ballots, and
 //     512 threads emit the set bits of their 32-chunk words in order.
+// topk_wide_kernel (up to 65536 chunks): the same selection with more keys per
+//   thread and nothing staged in LDS but the threshold bin.
 // topk_kernel (longer contexts): 8-bit digits, with the keys staged in LDS when
 //   they fit and re-read from memory in every pass otherwise.
 #include "lsa_internal.h"
@@ -224,6 +226,34 @@ __device__ __forceinline__ uint32_t lane_bcast(uint32_t v, int lane) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+// One wavefront: the bin of the 1024-bin histogram h that holds the kr-th
+// largest key, counting from the top bin down; updates kr to the number of keys
+// still to take from that bin.
+__device__ __forceinline__ uint32_t wave_pick(const uint32_t* h, uint32_t& kr) {
+  const int lane = threadIdx.x & 63;
+  const uint4* h4 = reinterpret_cast<const uint4*>(h) + lane * 4;  // lane l owns bins 16l .. 16l+15
+  uint32_t sum = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint4 x = h4[q];
+    sum += x.x + x.y + x.z + x.w;
+  }
+  const uint32_t incl = wave_scan_incl(sum);
+  const uint32_t above = lane_bcast(incl, 63) - incl;  // keys in the bins of higher lanes
+  const int L = __builtin_ctzll(__ballot(above < kr && above + sum >= kr));
+  const uint32_t krl = kr - lane_bcast(above, L);
+  // lane i < 16 takes bin 16L + 15 - i (descending), then a row scan
+  const uint32_t c = lane < 16 ? h[16 * L + 15 - lane] : 0u;
+  uint32_t ci = c;
+  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x111, 0xF, 0xF, false);  // row_shr:1
+  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x112, 0xF, 0xF, false);  // row_shr:2
+  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x114, 0xF, 0xF, false);  // row_shr:4
+  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x118, 0xF, 0xF, false);  // row_shr:8
+  const int i = __builtin_ctzll(__ballot(lane < 16 && ci >= krl && ci - c < krl));
+  kr = krl - (lane_bcast(ci, i) - lane_bcast(c, i));
+  return (uint32_t)(16 * L + 15 - i);
+}
+
 // One wavefront: among the keys src[0 .. m) that match (prefix, pmask), find
 // the bin of the next 10-bit digit (below bit `shift`) holding the kr-th
 // largest; h is a private LDS area of 1024 words and src is readable up to the
@@ -247,26 +277,7 @@ __device__ __forceinline__ uint32_t wave_digit(const uint32_t* src, int m, uint3
       if (c0 + u * 64 + lane < m && (v[u] & pmask) == prefix) atomicAdd(&h[(v[u] >> shift) & 1023u], 1u);
   }
   __builtin_amdgcn_wave_barrier();
-  uint32_t sum = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint4 x = h4[q];
-    sum += x.x + x.y + x.z + x.w;
-  }
-  const uint32_t incl = wave_scan_incl(sum);
-  const uint32_t above = lane_bcast(incl, 63) - incl;  // keys in the bins of higher lanes
-  const int L = __builtin_ctzll(__ballot(above < kr && above + sum >= kr));
-  const uint32_t krl = kr - lane_bcast(above, L);
-  // lane i < 16 takes bin 16L + 15 - i (descending), then a row scan
-  const uint32_t c = lane < 16 ? h[16 * L + 15 - lane] : 0u;
-  uint32_t ci = c;
-  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x111, 0xF, 0xF, false);  // row_shr:1
-  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x112, 0xF, 0xF, false);  // row_shr:2
-  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x114, 0xF, 0xF, false);  // row_shr:4
-  ci += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ci, 0x118, 0xF, 0xF, false);  // row_shr:8
-  const int i = __builtin_ctzll(__ballot(lane < 16 && ci >= krl && ci - c < krl));
-  kr = krl - (lane_bcast(ci, i) - lane_bcast(c, i));
-  return (uint32_t)(16 * L + 15 - i);
+  return wave_pick(h, kr);
 }
 
 // Raw 32-bit buffer view of `bytes` bytes at p (gfx9 buffer descriptor: no
@@ -504,6 +515,226 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
       out[pos++] = sa.map != nullptr ? (int32_t)map_lds[i] : i;
       kept &= kept - 1u;
     }
+  }
+  finish_count(t, sa, b, k, out, sel_count, tid, kSelThreads);
+}
+
+// ---------------------------------------------------------------------------
+// More than 16384 and up to 65536 chunks per (sequence, query): the same
+// selection with KPT = 24, 40 or 64 keys per thread in registers (LDS has no
+// room to stage them).  The candidates of the threshold bin are placed by
+// ballots instead of the histogram's return values (one register per key
+// less), a bin too large to pack is refined by digits over the registers, and
+// a thread emits 64 consecutive chunks.  Bound: instruction issue and latency
+// on one compute unit.  40,003 keys, 1,638 kept: 75 us with the streaming
+// topk_kernel, which reads the keys six times, 19 us here.
+constexpr int kWideMaxN = 65536;
+
+template <int MODE, bool RECALL, int KPT>
+__global__ void __launch_bounds__(kSelThreads)
+topk_wide_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __restrict__ out_idx,
+                 int64_t pitch_seq, int64_t pitch_q, int32_t* __restrict__ sel_count, SelectArgs sa) {
+  __shared__ __align__(16) uint32_t hist[4096 * kSelSub];
+  __shared__ uint32_t cand[kSelCand + 512];  // + the read-ahead of the last batch
+  __shared__ uint32_t tot[2][kSelWaves];
+  __shared__ uint64_t bm_gt[kWideMaxN / 64], bm_eq[kWideMaxN / 64];
+  __shared__ uint32_t sh[4], sh_n;
+
+  const int Q = t.n_lookahead;
+  const int b = blockIdx.x / Q, j = blockIdx.x - b * Q;
+  const int nb = t.n[b];
+  const int n = sa.dev_n != nullptr ? min(nb, max(sa.dev_n[b], 0)) : nb;
+  int k = min(t.keep[b], n);
+  const int tid = threadIdx.x, lane = tid & 63, sub = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t* s = scores + (int64_t)Q * t.chunk_off[b] + (int64_t)j * nb;
+  int32_t* out = out_idx + b * pitch_seq + j * pitch_q;
+  if (k == 0) {  // no keys (uniform across the workgroup)
+    finish_count(t, sa, b, 0, out, sel_count, tid, kSelThreads);
+    return;
+  }
+
+  // Key i = q * 1024 + tid sits in slot q of thread tid; slots past the end
+  // hold 0 and stay out of every histogram, as the recall's dropped keys do.
+  uint32_t kk[KPT];
+  {
+    const __amdgpu_buffer_rsrc_t src = raw_buffer(s, (uint32_t)n * 4u);
+#pragma unroll
+    for (int q = 0; q < KPT; ++q)
+      kk[q] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(src, tid * 4, q * kSelThreads * 4, 0);
+  }
+#pragma unroll
+  for (int q = 0; q < kSelSub; ++q)
+    reinterpret_cast<uint4*>(hist)[q * kSelThreads + tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) sh_n = 0u;
+  if constexpr (MODE != kKeysReady || RECALL) {
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) kk[q] = q * kSelThreads + tid < n ? order_key<MODE>(kk[q]) : 0u;
+  }
+  if constexpr (RECALL) {
+    // the largest over the indexer layers; keys below the key of +0.0 are not
+    // recalled and become 0
+    for (int l = 1; l < sa.n_layers; ++l) {
+      const __amdgpu_buffer_rsrc_t srcl = raw_buffer(s + l * sa.layer_stride, (uint32_t)n * 4u);
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) {
+        const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(srcl, tid * 4, q * kSelThreads * 4, 0);
+        if (q * kSelThreads + tid < n) kk[q] = max(kk[q], order_key<MODE>(v));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) kk[q] = kk[q] >= 0x80000000u ? kk[q] : 0u;
+  }
+  __syncthreads();
+  if constexpr (RECALL) {
+    uint32_t nn = 0;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) nn += (uint32_t)__popcll(__ballot(kk[q] != 0u));
+    if (lane == 0) atomicAdd(&sh_n, nn);
+  }
+  auto counts = [&](int q) { return RECALL ? kk[q] != 0u : q * kSelThreads + tid < n; };
+  // first digit: top 12 bits
+#pragma unroll
+  for (int q = 0; q < KPT; ++q)
+    if (counts(q)) atomicAdd(&hist[(kk[q] >> 20) * kSelSub + sub], 1u);
+  __syncthreads();
+  if constexpr (RECALL) {
+    k = min(k, (int)sh_n);
+    if (k == 0) {  // nothing recalled (uniform across the workgroup)
+      finish_count(t, sa, b, 0, out, sel_count, tid, kSelThreads);
+      return;
+    }
+  }
+  // bin B0 holding the k-th largest key: thread t owns bins 4t .. 4t+3
+  {
+    const uint4* h4 = reinterpret_cast<const uint4*>(hist) + 4 * tid;
+    uint32_t c[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint4 x = h4[q];
+      c[q] = x.x + x.y + x.z + x.w;
+    }
+    const uint32_t incl = wave_scan_incl(c[0] + c[1] + c[2] + c[3]);
+    if (lane == 63) tot[0][wave] = incl;
+    __syncthreads();
+    const uint32_t wt = lane < kSelWaves ? tot[0][lane] : 0u;
+    const uint32_t after = lane_bcast(wave_scan_incl(lane > wave ? wt : 0u), 63);
+    uint32_t cum = after + lane_bcast(incl, 63) - incl;  // keys in the bins above this thread's
+    const uint32_t kr = (uint32_t)k;
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+      if (cum < kr && cum + c[q] >= kr) {
+        sh[0] = 4u * tid + q;
+        sh[1] = kr - cum;
+        sh[2] = c[q];
+      }
+      cum += c[q];
+    }
+    if (tid == 0) sh_n = 0u;
+  }
+  __syncthreads();
+  const uint32_t B0 = sh[0], m = sh[2];
+  uint32_t krem = sh[1];
+  uint32_t prefix = B0 << 20;
+
+  // the last 20 bits as two 10-bit digits
+  if (m <= (uint32_t)kSelCand) {
+    // the keys of bin B0 to the candidate list, one LDS atomic per wavefront
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) mine += (uint32_t)__popcll(__ballot((kk[q] >> 20) == B0 && counts(q)));
+    uint32_t at = 0;
+    if (lane == 0 && mine != 0u) at = atomicAdd(&sh_n, mine);
+    at = lane_bcast(at, 0);
+    uint32_t bin = B0;  // compared again: the masks of the count would not fit the scalar registers
+    asm volatile("" : "+v"(bin));
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      const bool in = (kk[q] >> 20) == bin && counts(q);
+      const uint64_t bal = __ballot(in);
+      if (bal != 0ull) {  // wave-uniform
+        if (in)
+          cand[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] =
+              kk[q];
+        at += (uint32_t)__popcll(bal);
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      uint32_t kr = krem;
+      prefix |= wave_digit(cand, (int)m, prefix, 0xFFF00000u, 10, kr, hist) << 10;
+      prefix |= wave_digit(cand, (int)m, prefix, 0xFFFFFC00u, 0, kr, hist);
+      if (lane == 0) {
+        sh[0] = prefix;
+        sh[1] = kr;
+      }
+    }
+    __syncthreads();
+  } else {
+    for (int shift = 10; shift >= 0; shift -= 10) {
+      const uint32_t pmask = 0xFFFFFFFFu << (shift + 10);
+      hist[tid] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < KPT; ++q)
+        if ((kk[q] & pmask) == prefix && counts(q)) atomicAdd(&hist[(kk[q] >> shift) & 1023u], 1u);
+      __syncthreads();
+      if (wave == 0) {
+        uint32_t kr = krem;
+        const uint32_t d = wave_pick(hist, kr);
+        if (lane == 0) {
+          sh[0] = prefix | (d << shift);
+          sh[1] = kr;
+        }
+      }
+      __syncthreads();
+      prefix = sh[0];
+      krem = sh[1];
+    }
+  }
+  const uint32_t T = sh[0];  // the k-th largest key; krem keys equal to T are kept
+  krem = sh[1];
+
+  // the ballot of one wave and slot covers the 64 consecutive chunks of word
+  // 16 q + wave
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) {
+    const uint64_t g = __ballot(kk[q] > T);
+    const uint64_t e = __ballot(kk[q] == T);
+    if (lane == 0) {
+      bm_gt[q * kSelWaves + wave] = g;
+      bm_eq[q * kSelWaves + wave] = e;
+    }
+  }
+  __syncthreads();
+  // emission in chunk order: thread v owns chunks 64v .. 64v+63
+  uint64_t g = 0, e = 0;
+  if (tid < KPT * kSelWaves) {
+    const int valid = n - 64 * tid;  // chunk ids past n are padding
+    const uint64_t live = valid >= 64 ? ~0ull : valid > 0 ? (1ull << valid) - 1ull : 0ull;
+    g = bm_gt[tid] & live;
+    e = bm_eq[tid] & live;
+  }
+  const uint32_t cg = (uint32_t)__popcll(g), ce = (uint32_t)__popcll(e);
+  const uint32_t ig = wave_scan_incl(cg), ie = wave_scan_incl(ce);
+  if (lane == 63) {
+    tot[0][wave] = ig;
+    tot[1][wave] = ie;
+  }
+  __syncthreads();
+  const uint32_t wg = lane < wave ? tot[0][lane & (kSelWaves - 1)] : 0u;
+  const uint32_t we = lane < wave ? tot[1][lane & (kSelWaves - 1)] : 0u;
+  const uint32_t gb = lane_bcast(wave_scan_incl(wg), 63) + ig - cg;
+  const uint32_t eb = lane_bcast(wave_scan_incl(we), 63) + ie - ce;
+  uint64_t kept = g;
+  for (uint32_t r = eb < krem ? krem - eb : 0u; e != 0ull && r != 0u; --r) {
+    kept |= e & (0ull - e);  // lowest remaining chunk equal to T
+    e &= e - 1ull;
+  }
+  uint32_t pos = gb + min(eb, krem);
+  while (kept != 0ull) {
+    out[pos++] = emitted(sa, b, 64 * tid + __builtin_ctzll(kept));
+    kept &= kept - 1ull;
   }
   finish_count(t, sa, b, k, out, sel_count, tid, kSelThreads);
 }
@@ -788,6 +1019,15 @@ hipError_t launch_topk_keys(const SeqTable& t, const uint32_t* scores, int32_t* 
   else if (n_max <= kSelMaxN)
     hipLaunchKernelGGL((topk_select_kernel<MODE, RECALL, kSelKPT>), grid, dim3(kSelThreads), 0, s, t, scores,
                        out_idx, pitch_seq, pitch_q, sel_count, sa);
+  else if (n_max <= 24 * kSelThreads)
+    hipLaunchKernelGGL((topk_wide_kernel<MODE, RECALL, 24>), grid, dim3(kSelThreads), 0, s, t, scores, out_idx,
+                       pitch_seq, pitch_q, sel_count, sa);
+  else if (n_max <= 40 * kSelThreads)
+    hipLaunchKernelGGL((topk_wide_kernel<MODE, RECALL, 40>), grid, dim3(kSelThreads), 0, s, t, scores, out_idx,
+                       pitch_seq, pitch_q, sel_count, sa);
+  else if (n_max <= kWideMaxN)
+    hipLaunchKernelGGL((topk_wide_kernel<MODE, RECALL, 64>), grid, dim3(kSelThreads), 0, s, t, scores, out_idx,
+                       pitch_seq, pitch_q, sel_count, sa);
   else
     hipLaunchKernelGGL((topk_kernel<MODE, RECALL>), grid, dim3(kThreads), 0, s, t, scores, out_idx, pitch_seq,
                        pitch_q, sel_count, sa);
