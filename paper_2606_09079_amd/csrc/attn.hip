@@ -12,21 +12,22 @@
 // fp32; the softmax weights P enter the PV product as bf16 hi + lo parts (two
 // MFMAs per product), which keeps ~16 significant bits.
 //
-// attn_split_kernel (rows <= 16) on v_mfma_f32_16x16x32_bf16.  The 4 waves of
+// attn_split_kernel (rows <= 32) on v_mfma_f32_16x16x32_bf16.  The 4 waves of
 //   a workgroup take every fourth tile of the split (wave w: tiles w, w + 4,
 //   ...), each streaming its own tiles straight into registers (1 KiB per load
 //   instruction, nontemporal hint, two tiles in flight per wave), and merge
 //   their (m, l, O) states through LDS.  Interleaved tiles keep the four waves
 //   of a workgroup within a tile of each other where consecutive quarters left
 //   them waiting for the slowest at the merge.
-//   * QK computes S^T = K Q^T with 16 tokens as M and 16 query rows as N.  The
+//   * QK computes S^T = K Q^T with 16 tokens as M and 16 query rows as N (one
+//     or two blocks of rows).  The
 //     cache stores each (chunk, head) block in MFMA operand order, and the M
 //     rows of the two 16-token MFMAs of a tile are tokens 8a+0..3 and 8a+4..7,
 //     so after the product each lane holds the 8 consecutive tokens
 //     8*(lane/16)..+7 of query row lane%16 -- the A-operand layout PV needs.
 //   * PV computes O = P V with the tile's 32 tokens as K and 16 head dims per
 //     MFMA as N.
-// attn_rows_kernel (17..128 rows) on v_mfma_f32_32x32x16_bf16.  Every wave
+// attn_rows_kernel (33..128 rows) on v_mfma_f32_32x32x16_bf16.  Every wave
 //   owns 32 rows and needs every tile, so each tile is copied once per
 //   workgroup from HBM into LDS (global->LDS copies into MFMA operand order,
 //   three tiles ahead, five 16 KiB buffers).  QK computes S^T = K Q^T and PV
@@ -259,11 +260,13 @@ __device__ __forceinline__ void merge_few(const SeqTable& t, const AttnArgs& a, 
   if (slice == 0 && a.lse != nullptr) a.lse[orow] = (M + __log2f(L)) * kLn2;
 }
 
-template <int C, bool MERGE>
+// RB: blocks of 16 query rows, 1 or 2 (rows <= 16 RB), against the same K/V
+// registers.
+template <int C, bool MERGE, int RB>
 __global__ void __launch_bounds__(kThreads, 2)  // 2 waves per SIMD: <= 256 registers
 attn_split_kernel(SeqTable t, AttnArgs a) {
-  __shared__ float sm_o[kAttnWaves][16][kOPad];
-  __shared__ float sm_m[kAttnWaves][16], sm_l[kAttnWaves][16];
+  __shared__ float sm_o[kAttnWaves][16 * RB][kOPad];
+  __shared__ float sm_m[kAttnWaves][16 * RB], sm_l[kAttnWaves][16 * RB];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -288,25 +291,31 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
   const int T0 = split_first(sd.wg0 + g * ns, s, ns, nTall), T1 = split_first(sd.wg0 + g * ns, s + 1, ns, nTall);
   // wave w takes tiles T0 + w, T0 + w + 4, ... of the split
 
-  // ---- query operand: row n16 (rows <= 16 here)
-  bf16x8 qb[4];
-  {
-    const int row = n16;
+  // ---- query operands: row 16 rb + n16 of block rb
+  bf16x8 qb[RB][4];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = 16 * rb + n16;
     if (row < rows) {
       const int tq = row / G, h = g * G + row % G;
       const uint16_t* qp = a.q + (((int64_t)b * n_qtok + tq) * n_q_heads + h) * kHeadDim + 8 * kg;
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) qb[jj] = load8(qp + 32 * jj);
+      for (int jj = 0; jj < 4; ++jj) qb[rb][jj] = load8(qp + 32 * jj);
     } else {
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) qb[jj] = bf16x8{};
+      for (int jj = 0; jj < 4; ++jj) qb[rb][jj] = bf16x8{};
     }
   }
 
-  f32x4 o[8];
+  f32x4 o[RB][8];
+  float m_run[RB], l_run[RB];
 #pragma unroll
-  for (int nb = 0; nb < 8; ++nb) o[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
+  for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+    for (int nb = 0; nb < 8; ++nb) o[rb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[rb] = -INFINITY;
+    l_run[rb] = 0.f;
+  }
 
   // Tiles T0 + wave + 4 i of the kept list (i < nT); tile T is tile T % TPC of
   // kept chunk T / TPC.  The split's chunk ids are fetched 64 at a time into a
@@ -345,51 +354,6 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
 
   auto compute_tile = [&](const bf16x8(&kt)[8], bf16x8(&vt)[8], int lim) {
     if (lim <= 0) return;  // wave-uniform: the tile lies past the context end
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[jj], qb[jj], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[4 + jj], qb[jj], s1, 0, 0, 0);
-    }
-    // lane holds logits of query row n16 for tile tokens 8kg + 0..7
-    float x[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      x[i] *= a.scale_log2e;
-      mx = fmaxf(mx, x[i]);
-    }
-    if (lim < 32) {  // the context ends inside this tile: no weight for tokens 8 kg + i >= lim
-      mx = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        x[i] = 8 * kg + i < lim ? x[i] : -INFINITY;
-        mx = fmaxf(mx, x[i]);
-      }
-    }
-    mx = col_max(mx);  // finite: token 0 of the tile exists
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = fast_exp2(m_run - m_new);
-    f32x8 p;
-    float psum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      p[i] = fast_exp2(x[i] - m_new);
-      psum += p[i];
-    }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-    if (__ballot(alpha != 1.f) != 0ull) {
-      // O rows of this lane are 4kg..4kg+3; their alphas live in lanes 4kg+r
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float ar = __shfl(alpha, 4 * kg + r);
-#pragma unroll
-        for (int nb = 0; nb < 8; ++nb) o[nb][r] *= ar;
-      }
-    }
-    bf16x8 ph, pl;
-    split_bf16(p, ph, pl);
     if (lim < 32) {
       // the V slots of tokens past the context end may hold anything, NaN
       // included (not yet written): zero them, as a zero weight cancels only
@@ -403,9 +367,56 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
       for (int nb = 0; nb < 8; ++nb) vt[nb] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vt[nb]) & keep);
     }
 #pragma unroll
-    for (int nb = 0; nb < 8; ++nb) {
-      o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vt[nb], o[nb], 0, 0, 0);
-      o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, vt[nb], o[nb], 0, 0, 0);
+    for (int rb = 0; rb < RB; ++rb) {
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[jj], qb[rb][jj], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[4 + jj], qb[rb][jj], s1, 0, 0, 0);
+      }
+      // lane holds logits of query row 16 rb + n16 for tile tokens 8kg + 0..7
+      float x[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
+      float mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) mx = fmaxf(mx, x[i]);
+      if (lim < 32) {  // the context ends inside this tile: no weight for tokens 8 kg + i >= lim
+        mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          x[i] = 8 * kg + i < lim ? x[i] : -INFINITY;
+          mx = fmaxf(mx, x[i]);
+        }
+      }
+      // max over raw logits (the scale is positive), then p = exp2(x * scale - m);
+      // finite: token 0 of the tile exists
+      const float m_new = fmaxf(m_run[rb], col_max(mx) * a.scale_log2e);
+      const float alpha = fast_exp2(m_run[rb] - m_new);
+      f32x8 p;
+      float psum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        p[i] = fast_exp2(fmaf(x[i], a.scale_log2e, -m_new));
+        psum += p[i];
+      }
+      l_run[rb] = l_run[rb] * alpha + psum;
+      m_run[rb] = m_new;
+      if (__ballot(alpha != 1.f) != 0ull) {
+        // O rows of this lane are 4kg..4kg+3; their alphas live in lanes 4kg+r
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float ar = __shfl(alpha, 4 * kg + r);
+#pragma unroll
+          for (int nb = 0; nb < 8; ++nb) o[rb][nb][r] *= ar;
+        }
+      }
+      bf16x8 ph, pl;
+      split_bf16(p, ph, pl);
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb) {
+        o[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vt[nb], o[rb][nb], 0, 0, 0);
+        o[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, vt[nb], o[rb][nb], 0, 0, 0);
+      }
+      if (RB > 1) __builtin_amdgcn_sched_barrier(0);  // one block's temporaries at a time
     }
   };
 
@@ -421,20 +432,26 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
       compute_tile(kb2, vb2, lim_b);
     }
   }
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    l_run[rb] += __shfl_xor(l_run[rb], 16);
+    l_run[rb] += __shfl_xor(l_run[rb], 32);
+  }
 
   // ---- this split's partials: rows of the (b, g) group, [unit][rows_pad]
   const int rows_pad = a.rows_pad;
   const int64_t unit = (int64_t)sd.wg0 + (int64_t)g * ns + s;
   {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) sm_o[wave][4 * kg + r][16 * nb + n16] = o[nb][r];
-    if (kg == 0) {
-      sm_m[wave][n16] = m_run;
-      sm_l[wave][n16] = l_run;
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) sm_o[wave][16 * rb + 4 * kg + r][16 * nb + n16] = o[rb][nb][r];
+      if (kg == 0) {
+        sm_m[wave][16 * rb + n16] = m_run[rb];
+        sm_l[wave][16 * rb + n16] = l_run[rb];
+      }
     }
     __syncthreads();
     for (int idx = tid; idx < a.rows * kHeadDim; idx += kThreads) {
@@ -496,7 +513,7 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
 }
 
 
-// More than 16 query rows per KV head (rows = G * n_qtok, up to 128).  One
+// More than 32 query rows per KV head (rows = G * n_qtok, up to 128).  One
 // workgroup per (sequence, kv head, split) serves all the rows, so each K/V
 // tile is fetched from HBM once: every wave copies 4 of the tile's 16 one-KiB
 // pieces (K pieces 0-7, V pieces 8-15) straight into LDS with
@@ -915,12 +932,14 @@ attn_combine_few_kernel(SeqTable t, AttnArgs a, int n_rows) {
 template <int C>
 hipError_t launch_c(const SeqTable& t, const AttnArgs& a, hipStream_t s) {
   const dim3 grid(t.wg_off[t.batch]);
-  if (a.rows > 16)
+  if (a.rows > kAttnSplitRows)
     hipLaunchKernelGGL((attn_rows_kernel<C>), grid, dim3(kThreads), 0, s, t, a);
+  else if (a.rows > 16)
+    hipLaunchKernelGGL((attn_split_kernel<C, false, 2>), grid, dim3(kThreads), 0, s, t, a);
   else if (a.arrive != nullptr)
-    hipLaunchKernelGGL((attn_split_kernel<C, true>), grid, dim3(kThreads), 0, s, t, a);
+    hipLaunchKernelGGL((attn_split_kernel<C, true, 1>), grid, dim3(kThreads), 0, s, t, a);
   else
-    hipLaunchKernelGGL((attn_split_kernel<C, false>), grid, dim3(kThreads), 0, s, t, a);
+    hipLaunchKernelGGL((attn_split_kernel<C, false, 1>), grid, dim3(kThreads), 0, s, t, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.arrive != nullptr && a.rows <= kAttnRowsPerWave) return hipSuccess;  // the split kernel merged the splits

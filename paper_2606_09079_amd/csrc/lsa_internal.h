@@ -60,6 +60,13 @@ struct AttnArgs {
 constexpr int kAttnWaves = 4;          // waves per workgroup
 constexpr int kAttnRowsPerWave = 16;   // MFMA tile rows
 constexpr int kHeadDim = 128;
+// Query rows per KV head up to which the split kernel serves: 17 to 32 rows as
+// two 16-row blocks against the same K/V registers.  32 rows, 110,500 kept
+// tokens: 83 us against 90 with the many-rows kernel (whose four waves would
+// leave three without a row block); 24 rows, 16 sequences: 238 against 260.
+// With four blocks (33 to 64 rows) the registers do not suffice: 295 us
+// against 108.
+constexpr int kAttnSplitRows = 32;
 // Split-K sizing: the attention grid is sized to one resident round of the
 // MI355X (256 CUs x 2 workgroups of 256 threads at <= 256 registers).  With
 // at most kFewSequences sequences the split kernel (<= 16 rows) runs one
