@@ -260,13 +260,19 @@ __device__ __forceinline__ void merge_few(const SeqTable& t, const AttnArgs& a, 
   if (slice == 0 && a.lse != nullptr) a.lse[orow] = (M + __log2f(L)) * kLn2;
 }
 
+// What the split kernel leaves: partials for a combine kernel; partials that
+// its last workgroup of each (b, g) merges; or, with one split per (b, g), the
+// output itself.
+enum SplitOut : int { kParts = 0, kMerge = 1, kDirect = 2 };
+
 // RB: blocks of 16 query rows, 1 or 2 (rows <= 16 RB), against the same K/V
-// registers.
-template <int C, bool MERGE, int RB>
-__global__ void __launch_bounds__(kThreads, 2)  // 2 waves per SIMD: <= 256 registers
+// registers.  W: waves per workgroup.
+template <int C, int OUT, int RB, int W>
+__global__ void __launch_bounds__(64 * W, 2)  // 2 waves per SIMD: <= 256 registers
 attn_split_kernel(SeqTable t, AttnArgs a) {
-  __shared__ float sm_o[kAttnWaves][16 * RB][kOPad];
-  __shared__ float sm_m[kAttnWaves][16 * RB], sm_l[kAttnWaves][16 * RB];
+  constexpr bool MERGE = OUT == kMerge;
+  __shared__ float sm_o[W][16 * RB][kOPad];
+  __shared__ float sm_m[W][16 * RB], sm_l[W][16 * RB];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -289,7 +295,7 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
   const int cnt = count_is_keep ? min(sd.keep, n_b) : min(max(a.sel_count[b], 0), sel_pitch);
   const int nTall = cnt * TPC;
   const int T0 = split_first(sd.wg0 + g * ns, s, ns, nTall), T1 = split_first(sd.wg0 + g * ns, s + 1, ns, nTall);
-  // wave w takes tiles T0 + w, T0 + w + 4, ... of the split
+  // wave w takes tiles T0 + w, T0 + w + W, ... of the split
 
   // ---- query operands: row 16 rb + n16 of block rb
   bf16x8 qb[RB][4];
@@ -317,11 +323,11 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
     l_run[rb] = 0.f;
   }
 
-  // Tiles T0 + wave + 4 i of the kept list (i < nT); tile T is tile T % TPC of
+  // Tiles T0 + wave + W i of the kept list (i < nT); tile T is tile T % TPC of
   // kept chunk T / TPC.  The split's chunk ids are fetched 64 at a time into a
   // register (one per lane) and read back with readlane, so no scalar load
   // sits between consecutive tiles.
-  const int nT = T1 - T0 > wave ? (T1 - T0 - wave + kAttnWaves - 1) / kAttnWaves : 0;
+  const int nT = T1 - T0 > wave ? (T1 - T0 - wave + W - 1) / W : 0;
   const int pos0 = T0 / TPC;
   const int npos = nT > 0 ? (T1 - 1) / TPC - pos0 + 1 : 0;
   const int32_t* sel = a.sel_idx + (int64_t)b * sel_pitch + pos0;
@@ -335,7 +341,7 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
   // Returns how many of the tile's tokens exist: 32, or fewer in the last
   // chunk of a context that ends inside it (and <= 0 for a tile past the end).
   auto load_tile = [&](int i, bf16x8(&kt)[8], bf16x8(&vt)[8]) -> int {
-    const int T = T0 + wave + kAttnWaves * i;
+    const int T = T0 + wave + W * i;
     const int j = T / TPC - pos0, tt = T % TPC;
     if (j - sel_base >= 64) {  // wave-uniform: next window of chunk ids
       sel_base = j & ~63;
@@ -454,19 +460,25 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
       }
     }
     __syncthreads();
-    for (int idx = tid; idx < a.rows * kHeadDim; idx += kThreads) {
+    for (int idx = tid; idx < a.rows * kHeadDim; idx += 64 * W) {
       const int r = idx / kHeadDim, e = idx % kHeadDim;
       float M = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, sm_m[w][r]);
+      for (int w = 0; w < W; ++w) M = fmaxf(M, sm_m[w][r]);
       float acc = 0.f, L = 0.f;
       if (M != -INFINITY) {
 #pragma unroll
-        for (int w = 0; w < kAttnWaves; ++w) {
+        for (int w = 0; w < W; ++w) {
           const float f = fast_exp2(sm_m[w][r] - M);
           acc += f * sm_o[w][r][e];
           L += f * sm_l[w][r];
         }
+      }
+      if constexpr (OUT == kDirect) {
+        const int64_t orow = out_row(a, b, g, r);
+        a.out[orow * kHeadDim + e] = acc * (L > 0.f ? 1.f / L : 0.f);  // an empty kept set gives out = 0, lse = -inf
+        if (e == 0 && a.lse != nullptr) a.lse[orow] = (M + __log2f(L)) * kLn2;
+        continue;
       }
       float* po = a.part_o + (unit * rows_pad + r) * kHeadDim + e;
       float* pml = a.part_ml + (unit * rows_pad + r) * 2;
@@ -486,7 +498,7 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
       }
     }
   }
-  if constexpr (!MERGE) return;  // a combine kernel merges the splits
+  if constexpr (!MERGE) return;  // a combine kernel merges the splits, or there is one
 
   // The last of the ns workgroups of (b, g) to arrive merges the splits.  A
   // workgroup counts itself in only once its partials are stored (every
@@ -509,7 +521,7 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
   if (!sh_last) return;
   // (the host sets arrive only with at most kFewSplits splits: merge_few's order)
   const DeviceParts pp(t, a);
-  for (int role = tid; role < a.rows * kSlices; role += kThreads) merge_few(t, a, pp, b, g, role / kSlices, role % kSlices);
+  for (int role = tid; role < a.rows * kSlices; role += 64 * W) merge_few(t, a, pp, b, g, role / kSlices, role % kSlices);
 }
 
 
@@ -932,14 +944,18 @@ attn_combine_few_kernel(SeqTable t, AttnArgs a, int n_rows) {
 template <int C>
 hipError_t launch_c(const SeqTable& t, const AttnArgs& a, hipStream_t s) {
   const dim3 grid(t.wg_off[t.batch]);
+  if (a.one_split) {
+    hipLaunchKernelGGL((attn_split_kernel<C, kDirect, 1, kOneSplitWaves>), grid, dim3(64 * kOneSplitWaves), 0, s, t, a);
+    return hipGetLastError();
+  }
   if (a.rows > kAttnSplitRows)
     hipLaunchKernelGGL((attn_rows_kernel<C>), grid, dim3(kThreads), 0, s, t, a);
   else if (a.rows > 16)
-    hipLaunchKernelGGL((attn_split_kernel<C, false, 2>), grid, dim3(kThreads), 0, s, t, a);
+    hipLaunchKernelGGL((attn_split_kernel<C, kParts, 2, kAttnWaves>), grid, dim3(kThreads), 0, s, t, a);
   else if (a.arrive != nullptr)
-    hipLaunchKernelGGL((attn_split_kernel<C, true, 1>), grid, dim3(kThreads), 0, s, t, a);
+    hipLaunchKernelGGL((attn_split_kernel<C, kMerge, 1, kAttnWaves>), grid, dim3(kThreads), 0, s, t, a);
   else
-    hipLaunchKernelGGL((attn_split_kernel<C, false, 1>), grid, dim3(kThreads), 0, s, t, a);
+    hipLaunchKernelGGL((attn_split_kernel<C, kParts, 1, kAttnWaves>), grid, dim3(kThreads), 0, s, t, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.arrive != nullptr && a.rows <= kAttnRowsPerWave) return hipSuccess;  // the split kernel merged the splits

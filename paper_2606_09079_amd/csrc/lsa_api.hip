@@ -41,6 +41,7 @@ struct Plan {
   int32_t group = 0, rows = 0, rows_pad = 16;
   int64_t chunk_stride = 0, head_stride = 0;
   int64_t n_units = 0;
+  bool one_split = false;  // every (b, g) in one workgroup that writes the output
   size_t emb_elem = 0;
   // two-level path: history chunks (before the window) per sequence, and the
   // pitch of the recalled list
@@ -117,10 +118,32 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
     return std::min<int64_t>({(int64_t)tl->core_keep[b], (int64_t)p->keep[b], w0}) + (n - w0);
   };
   // First pass: the total kept-chunk bound, which sizes the splits.
-  int64_t sel_total = 0;
-  for (int b = 0; b < B; ++b) sel_total += kept_bound(b);
+  int64_t sel_total = 0, sel_most = 0;
+  for (int b = 0; b < B; ++b) {
+    sel_total += kept_bound(b);
+    sel_most = std::max(sel_most, kept_bound(b));
+  }
   const int tpc = C / 32;
+  P.one_split = rows <= 16 && sel_most * tpc <= kOneSplitTiles;
   const int target = rows <= 16 && B <= kFewSequences ? kTargetWorkgroupsFew : kTargetWorkgroups;
+  // Batches: the fewest tiles per split with which the grid stays within two
+  // resident rounds (0: splits in proportion, one round).  Splits in proportion
+  // round to whole ones, so some hold half as much again as others; equal
+  // ones, at twice the number, leave the dispatcher something to balance.
+  int64_t split_tiles = 0;
+  if (rows <= 16 && B > kFewSequences && !P.one_split &&
+      sel_total * tpc * p->n_kv_heads >= (int64_t)kBatchWorkgroups * kBatchTiles) {
+    int64_t lo = 1, hi = std::max<int64_t>(sel_most * tpc, 1);
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      int64_t wgs = 0;
+      for (int b = 0; b < B; ++b)
+        wgs += (int64_t)p->n_kv_heads * std::max<int64_t>(1, (kept_bound(b) * tpc + mid - 1) / mid);
+      if (wgs <= kBatchWorkgroups) hi = mid;
+      else lo = mid + 1;
+    }
+    split_tiles = lo;
+  }
   int64_t chunk_off = 0, wg_off = 0, swg_off = 0;
   for (int b = 0; b < B; ++b) {
     const int64_t L = p->ctx_tokens[b];
@@ -152,8 +175,9 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
     // whole grid is about `target`; at least one 32-token tile per split
     const double share = (double)target * (double)msel /
                          ((double)p->n_kv_heads * (double)std::max<int64_t>(sel_total, 1));
-    const int32_t ns = (int32_t)std::max<int64_t>(
-        1, std::min<int64_t>({std::llround(share), (int64_t)kMaxSplits, (int64_t)msel * tpc}));
+    const int64_t want = split_tiles ? ((int64_t)msel * tpc + split_tiles - 1) / split_tiles : std::llround(share);
+    const int32_t ns = P.one_split ? 1 : (int32_t)std::max<int64_t>(
+        1, std::min<int64_t>({want, (int64_t)kMaxSplits, (int64_t)msel * tpc}));
     t.n[b] = (int32_t)n;
     t.keep[b] = k;
     t.nsplit[b] = ns;
@@ -274,7 +298,7 @@ int max_splits(const Plan& P) {
 // splits.  The merge of 32 splits in one workgroup, and one more wait in each
 // of two workgroups per CU, cost more than the launch.
 bool merge_in_split(const Plan& P) {
-  return P.rows <= kAttnRowsPerWave && P.t.batch <= kFewSequences && max_splits(P) <= kFewSplits;
+  return !P.one_split && P.rows <= kAttnRowsPerWave && P.t.batch <= kFewSequences && max_splits(P) <= kFewSplits;
 }
 
 // count_is_keep: sel_count[b] is known to be min(keep[b], n_b) (the top-k of a
@@ -304,6 +328,7 @@ lsa_status run_attn(const lsa_problem* p, const Plan& P, const uint16_t* q, cons
   a.n_qtok = p->n_qtok;
   a.rows = P.rows;
   a.rows_pad = P.rows_pad;
+  a.one_split = P.one_split ? 1 : 0;
   a.few_splits = max_splits(P) <= kFewSplits ? 1 : 0;
   a.arrive = P.t.arrive;  // set (and zeroed by the scoring kernel) only where merge_in_split(P)
   LSA_HIP(launch_attn(P.t, a, p->chunk_size, s), "attention launch");

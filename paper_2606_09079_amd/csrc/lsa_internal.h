@@ -53,6 +53,7 @@ struct AttnArgs {
   int32_t rows_pad;      // partial rows per (b, g, split): rows rounded up to 16
   uint32_t* arrive;      // NULL: a combine kernel merges the splits.  Else one counter per (b, g), zero on
                          // entry: the last split workgroup of (b, g) to finish merges them (split kernel only)
+  int32_t one_split;     // 1: one split per (b, g), whose workgroup writes the output
   int32_t few_splits;    // 1: every sequence has at most 16 splits (the merge order of the few-split combine)
 };
 
@@ -77,6 +78,22 @@ constexpr int kTargetWorkgroups = 512;
 constexpr int kTargetWorkgroupsFew = 256;
 constexpr int kFewSequences = 8;
 constexpr int kFewSplits = 16;   // splits per (sequence, kv head) up to which the few-split merge order holds
+// More than kFewSequences sequences with at least kBatchTiles tiles per
+// workgroup: splits of equal length, at most kBatchWorkgroups in all.  Split + combine:
+// 32 sequences of 64K to 128K tokens at 10% 239 -> 193 us, 16 of them 120 ->
+// 106, 16 of 64K to 256K at 8% 161 -> 140; even batches 285 -> 257 (24) or
+// unchanged (16, 32).  With fewer tiles the extra partials cost what the balance
+// gains (5 tiles: 20.3 -> 20.8).  1,536 and 2,048 workgroups measured within
+// 2% of 1,024.
+constexpr int kBatchWorkgroups = 1024;
+constexpr int kBatchTiles = 24;
+// At most this many 32-token tiles per (sequence, KV head) and 16 rows: one
+// workgroup of kOneSplitWaves waves takes them all and writes the output itself.
+// One compute unit streams about 90 KB/us, so 16 tiles (256 KiB) take 7.0 us
+// against 7.9 with the split kernel's own merge and 8.5 with a combine launch;
+// 32 tiles take 9.4 against 8.4.
+constexpr int kOneSplitTiles = 16;
+constexpr int kOneSplitWaves = 8;
 constexpr int kMaxSplits = 256;  // splits per (sequence, kv head, row group)
 
 // How the selection reads its scores: raw float32 scores, raw int32 scores, or
