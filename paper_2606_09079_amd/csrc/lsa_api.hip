@@ -285,6 +285,14 @@ lsa_status run_topk(const lsa_problem* p, const Plan& P, bool keys_ready, const 
   return LSA_OK;
 }
 
+// Whether scoring and selection go in one launch, one workgroup per sequence.
+bool score_select_fits(const lsa_problem* p, const Plan& P) {
+  if (p->n_lookahead != 1) return false;
+  int n_max = 0;
+  for (int b = 0; b < P.t.batch; ++b) n_max = std::max(n_max, P.t.n[b]);
+  return n_max <= kScoreSelectMaxN && (int64_t)n_max * p->emb_dim * (int64_t)P.emb_elem <= kScoreSelectBytes;
+}
+
 int max_splits(const Plan& P) {
   int ns_max = 0;
   for (int b = 0; b < P.t.batch; ++b) ns_max = std::max(ns_max, P.t.nsplit[b]);
@@ -727,8 +735,13 @@ lsa_status lsa_decode_step(const lsa_problem* p, const void* query_emb, const vo
     P.t.arrive = reinterpret_cast<uint32_t*>(at(ws, P.off_arrive));
     P.t.n_arrive = p->batch * p->n_kv_heads;
   }
-  LSA_HIP(launch_score(P.t, p->emb_dtype, p->emb_dim, query_emb, chunk_emb, scores, true, s), "score launch");
-  LSA_TRY(run_topk(p, P, true, scores, sel, cnt, nullptr, ws, s));
+  if (score_select_fits(p, P)) {
+    LSA_HIP(launch_score_select(P.t, p->emb_dtype, p->emb_dim, query_emb, chunk_emb, sel, P.max_sel, cnt, s),
+            "score and select launch");
+  } else {
+    LSA_HIP(launch_score(P.t, p->emb_dtype, p->emb_dim, query_emb, chunk_emb, scores, true, s), "score launch");
+    LSA_TRY(run_topk(p, P, true, scores, sel, cnt, nullptr, ws, s));
+  }
   return run_attn(p, P, q, k_cache, v_cache, sel, cnt, softmax_scale, out, lse, ws, s, p->n_lookahead == 1);
 }
 

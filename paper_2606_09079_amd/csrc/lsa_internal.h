@@ -157,6 +157,15 @@ __device__ __forceinline__ void zero_arrivals(const SeqTable& t) {
       __hip_atomic_store(t.arrive + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// One launch for scoring and selecting short sequences (one query embedding),
+// up to kScoreSelectMaxN chunks and kScoreSelectBytes of embeddings each (past
+// that one compute unit reads them more slowly than the launch is worth):
+// writes the kept ids and counts as launch_topk does, and no scores.
+constexpr int kScoreSelectMaxN = 512;
+constexpr int64_t kScoreSelectBytes = 128 << 10;
+hipError_t launch_score_select(const SeqTable& t, int32_t emb_dtype, int32_t emb_dim, const void* qe, const void* E,
+                               int32_t* out_idx, int64_t out_pitch, int32_t* sel_count, hipStream_t s);
+
 // keys == true writes order keys instead of scores (for the fused step).
 hipError_t launch_score(const SeqTable& t, int32_t emb_dtype, int32_t emb_dim, const void* qe,
                         const void* E, void* scores, bool keys, hipStream_t s);

@@ -15,6 +15,8 @@
 //   I8  : v_dot4 int8 -> int32, exact (|s| <= D * 127^2 < 2^31 for D <= 512)
 // With bf16 embeddings and at least 4 lookahead queries the same product is a
 // dense [n_b x D] x [D x Q] contraction and runs on MFMA (score_mfma_kernel).
+#include <type_traits>
+
 #include "lsa_internal.h"
 
 namespace lsa {
@@ -129,6 +131,136 @@ score_kernel(SeqTable t, const uint8_t* __restrict__ qe, const uint8_t* __restri
     }
   }
   zero_arrivals(t);
+}
+
+// Selection of a short sequence by one wavefront, with no LDS and no barrier:
+// lane l holds the keys of entries 64 q + l in kk[q] (0 past n, and above 0
+// before).  The k-th
+// largest key is found bit by bit from the top: a bit stays set while at least
+// k keys reach the value, and when exactly k do, they are the selection.
+// emit(position, entry) is called for each kept entry, ascending; keys equal to
+// the k-th go in entry order while the quota lasts.  1 <= k <= n.
+template <int KPL, class Emit>
+__device__ __forceinline__ void wave_select(const uint32_t (&kk)[KPL], int n, int k, Emit emit) {
+  const int lane = threadIdx.x & 63;
+  uint32_t T = 0u;
+  bool whole = false;  // exactly the keys at or above T
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = T | (1u << bit);
+    int cnt = 0;
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) cnt += (int)__popcll(__ballot(kk[q] >= c));
+    if (cnt >= k) T = c;
+    if (cnt == k) {
+      whole = true;
+      break;
+    }
+  }
+  int rem = 0;  // keys equal to T to take
+  if (!whole) {
+    rem = k;
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) rem -= (int)__popcll(__ballot(kk[q] > T));
+  }
+  int pos = 0;
+#pragma unroll
+  for (int q = 0; q < KPL; ++q) {
+    uint64_t kept = __ballot(kk[q] > T);
+    uint64_t eq = __ballot(kk[q] == T && 64 * q + lane < n);
+    if (whole) {
+      kept |= eq;
+    } else {
+      for (; eq != 0ull && rem > 0; --rem) {
+        kept |= eq & (0ull - eq);  // lowest remaining entry equal to T
+        eq &= eq - 1ull;
+      }
+    }
+    if ((kept >> lane) & 1ull)
+      emit(pos + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u)),
+           64 * q + lane);
+    pos += (int)__popcll(kept);
+  }
+}
+
+// Scoring and selection of a short sequence in one workgroup, for one query
+// embedding: the dot products of score_kernel (same pieces, same reduction)
+// leave as order keys in LDS, and one wavefront keeps the k largest
+// (wave_select).  Bound: latency, and what one compute unit can stream (about
+// 90 KB/us), against two launches.  64 chunks of 1 KiB: 4.4 us against 2.8 +
+// 5.3; 128 KiB: 6.6 against 3.0 + 5.1; 256 KiB would take 9.9, so longer ones
+// keep the two kernels.
+constexpr int kSelThreads = 1024;
+
+template <int DT, int D>
+__global__ void __launch_bounds__(kSelThreads)
+score_select_kernel(SeqTable t, const uint8_t* __restrict__ qe, const uint8_t* __restrict__ E,
+                    int32_t* __restrict__ out_idx, int64_t pitch, int32_t* __restrict__ sel_count) {
+  using G = Geo<DT, D>;
+  constexpr int es = Elem<DT>::size;
+  constexpr int kRows = kSelThreads / G::lanes;  // rows per pass
+  constexpr int kBatch = 4;                      // passes in flight
+  __shared__ uint32_t keys[kScoreSelectMaxN];
+  const int b = blockIdx.x;
+  const int n = t.n[b], k = min(t.keep[b], n);
+  const int sub = threadIdx.x % G::lanes, rw = threadIdx.x / G::lanes;
+  const uint8_t* Eb = E + t.chunk_off[b] * (int64_t)(D * es);
+  const uint8_t* qj = qe + (int64_t)b * (D * es);
+  uint4 qv[G::ppl];
+#pragma unroll
+  for (int pp = 0; pp < G::ppl; ++pp) qv[pp] = *reinterpret_cast<const uint4*>(qj + (sub + pp * G::lanes) * 16);
+  for (int row0 = 0; row0 < n; row0 += kBatch * kRows) {
+    uint4 e[kBatch][G::ppl];
+#pragma unroll
+    for (int p = 0; p < kBatch; ++p) {
+      const int r = row0 + p * kRows + rw;
+#pragma unroll
+      for (int pp = 0; pp < G::ppl; ++pp)
+        e[p][pp] = r < n ? *reinterpret_cast<const uint4*>(Eb + (int64_t)r * (D * es) + (sub + pp * G::lanes) * 16)
+                         : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int p = 0; p < kBatch; ++p) {
+      const int r = row0 + p * kRows + rw;
+      uint32_t key;
+      if constexpr (DT == LSA_I8) {
+        int acc = 0;
+#pragma unroll
+        for (int pp = 0; pp < G::ppl; ++pp) acc = piece_dot_i8(e[p][pp], qv[pp], acc);
+#pragma unroll
+        for (int off = G::lanes / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+        key = int_score_key(acc);
+      } else {
+        float acc = 0.f;
+#pragma unroll
+        for (int pp = 0; pp < G::ppl; ++pp)
+          acc = (DT == LSA_F32) ? piece_dot_f32(e[p][pp], qv[pp], acc) : piece_dot_bf16(e[p][pp], qv[pp], acc);
+#pragma unroll
+        for (int off = G::lanes / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+        key = order_key<kKeysFromF32>(__float_as_uint(acc));
+      }
+      if (sub == 0 && r < n) keys[r] = key;
+    }
+  }
+  zero_arrivals(t);
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  int32_t* out = out_idx + b * pitch;
+  auto select = [&](auto slots) {
+    constexpr int kPer = decltype(slots)::value;
+    uint32_t kk[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = 64 * q + (int)threadIdx.x;
+      kk[q] = i < n ? keys[i] : 0u;
+    }
+    wave_select(kk, n, k, [&](int pos, int i) { out[pos] = i; });
+  };
+  if (n <= 64) select(std::integral_constant<int, 1>{});
+  else if (n <= 128) select(std::integral_constant<int, 2>{});
+  else if (n <= 256) select(std::integral_constant<int, 4>{});
+  else select(std::integral_constant<int, 8>{});
+  if (threadIdx.x == 0) sel_count[b] = k;
 }
 
 // Several lookahead queries with bf16 embeddings: the scores of a sequence are
@@ -249,6 +381,22 @@ hipError_t launch_dt(const SeqTable& t, int32_t D, const void* qe, const void* E
 }
 
 template <int DT>
+hipError_t launch_select_dt(const SeqTable& t, int32_t D, const void* qe, const void* E, int32_t* out, int64_t pitch,
+                            int32_t* cnt, hipStream_t s) {
+  const dim3 grid(t.batch), block(kSelThreads);
+  const auto* q8 = static_cast<const uint8_t*>(qe);
+  const auto* e8 = static_cast<const uint8_t*>(E);
+  switch (D) {
+    case 64: hipLaunchKernelGGL((score_select_kernel<DT, 64>), grid, block, 0, s, t, q8, e8, out, pitch, cnt); break;
+    case 128: hipLaunchKernelGGL((score_select_kernel<DT, 128>), grid, block, 0, s, t, q8, e8, out, pitch, cnt); break;
+    case 256: hipLaunchKernelGGL((score_select_kernel<DT, 256>), grid, block, 0, s, t, q8, e8, out, pitch, cnt); break;
+    case 512: hipLaunchKernelGGL((score_select_kernel<DT, 512>), grid, block, 0, s, t, q8, e8, out, pitch, cnt); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <int DT>
 int rows_dt(int32_t D) {
   switch (D) {
     case 64: return Geo<DT, 64>::rows_per_wg;
@@ -276,6 +424,16 @@ int score_rows_per_wg(int32_t emb_dtype, int32_t emb_dim, int32_t n_lookahead) {
     case LSA_BF16: return rows_dt<LSA_BF16>(emb_dim);
     case LSA_I8: return rows_dt<LSA_I8>(emb_dim);
     default: return 0;
+  }
+}
+
+hipError_t launch_score_select(const SeqTable& t, int32_t emb_dtype, int32_t emb_dim, const void* qe, const void* E,
+                               int32_t* out_idx, int64_t out_pitch, int32_t* sel_count, hipStream_t s) {
+  switch (emb_dtype) {
+    case LSA_F32: return launch_select_dt<LSA_F32>(t, emb_dim, qe, E, out_idx, out_pitch, sel_count, s);
+    case LSA_BF16: return launch_select_dt<LSA_BF16>(t, emb_dim, qe, E, out_idx, out_pitch, sel_count, s);
+    case LSA_I8: return launch_select_dt<LSA_I8>(t, emb_dim, qe, E, out_idx, out_pitch, sel_count, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
