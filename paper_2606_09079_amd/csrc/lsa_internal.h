@@ -98,14 +98,15 @@ constexpr int kMaxSplits = 256;  // splits per (sequence, kv head, row group)
 
 // How the selection reads its scores: raw float32 scores, raw int32 scores, or
 // scores the scoring kernel has already mapped to keys (the fused step).
-enum KeyMode : int { kKeysFromF32 = 0, kKeysFromI32 = 1, kKeysReady = 2 };
+// (kKeysReadyInt: keys of int_score_key, linear in the score.)
+enum KeyMode : int { kKeysFromF32 = 0, kKeysFromI32 = 1, kKeysReady = 2, kKeysReadyInt = 3 };
 
 // 32-bit key whose unsigned order is the score order.  float32: -0.0 is folded
 // onto +0.0, then positives get the sign bit set and negatives have every bit
 // flipped; int32: the sign bit is flipped.
 template <int MODE>
 __device__ __forceinline__ uint32_t order_key(uint32_t bits) {
-  if constexpr (MODE == kKeysReady) {
+  if constexpr (MODE == kKeysReady || MODE == kKeysReadyInt) {
     return bits;
   } else if constexpr (MODE == kKeysFromI32) {
     return bits ^ 0x80000000u;

@@ -1,0 +1,66 @@
+"""Top-k up to 16,384 chunks where one histogram over the scores' range settles
+the selection and where it must hand over to the radix passes: outliers that
+squeeze the other scores into one bin, many equal scores at the boundary, two
+clusters, subnormal and huge ranges, all-equal scores, at the edges of the
+kernel's variants.  Kept sets equal a stable sort of the same scores.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from test_gpu_topk_wide import _topk, _want
+
+pytestmark = pytest.mark.gpu
+
+
+def _scores(rng, n, kind):
+    x = rng.standard_normal((2, n)).astype(np.float32)
+    if kind == "outlier":
+        x[0, n // 2] = np.float32(1e30)
+        x[1, n // 3] = np.float32(-1e30)
+    elif kind == "boundary":  # 70 equal scores where the set ends
+        x = np.sort(x, axis=1)[:, ::-1].copy()
+        at = max(0, n // 10 - 35)
+        x[:, at:at + 70] = x[:, at:at + 1]
+        x = x[:, rng.permutation(n)]
+    elif kind == "clusters":
+        x[:, ::2] = x[:, ::2] * np.float32(1e-6) + np.float32(5.0)
+    elif kind == "subnormal":
+        x = (x * np.float32(1e-40)).astype(np.float32)
+    elif kind == "huge":
+        x = (np.sign(x) * np.float32(3e38) * rng.random((2, n)).astype(np.float32)).astype(np.float32)
+    elif kind == "equal":
+        x[:] = np.float32(-0.0)
+        x[:, 1::2] = np.float32(0.0)
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "outlier", "boundary", "clusters", "subnormal", "huge", "equal"])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 1023, 2048, 2049, 4097, 8192, 8193, 16384])
+def test_topk_spread(n, kind):
+    rng = np.random.default_rng(n + len(kind))
+    x = _scores(rng, n, kind)
+    for k in sorted({1, max(1, n // 10), max(1, n - 1), n}):
+        per_query, union = _topk(x, k, "f32", Q=2)
+        for j in range(2):
+            assert np.array_equal(per_query[j], _want(x[j], k)), (n, kind, k, j)
+        assert np.array_equal(union, np.union1d(_want(x[0], k), _want(x[1], k)))
+
+
+@pytest.mark.parametrize("n", [500, 4000, 16384])
+def test_recall_spread(n):
+    import torch
+    import paper_2606_09079_amd as L
+    rng = np.random.default_rng(n)
+    for kind in ("normal", "outlier", "huge", "equal"):
+        x = _scores(rng, n, kind)
+        r = x.max(0)
+        for k in (1, max(1, n // 8), n):
+            P, ix = L.Problem([64 * n], 64, [k], 8, 8), L.Indexer(2, 16, 64)
+            sel = torch.full((1, L.lsa_max_sel(P)), -1, dtype=torch.int32, device="cuda")
+            cnt = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+            L.lsa_recall_select(P, ix, torch.from_numpy(np.ascontiguousarray(x)).cuda(), sel, cnt)
+            torch.cuda.synchronize()
+            want = _want(r, min(k, int((r >= 0).sum())))
+            assert np.array_equal(sel.cpu().numpy()[0, :int(cnt.item())], want), (n, kind, k)
