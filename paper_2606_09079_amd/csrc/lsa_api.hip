@@ -100,7 +100,6 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
   t.batch = B;
   t.n_lookahead = p->n_lookahead;
   const int C = p->chunk_size;
-  const int srows = score_rows_per_wg(p->emb_dtype, p->emb_dim, p->n_lookahead);
   P.group = G;
   P.rows = rows;
   P.rows_pad = (rows + 15) / 16 * 16;  // partial rows per unit: whole 16-row MFMA blocks
@@ -118,11 +117,14 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
     return std::min<int64_t>({(int64_t)tl->core_keep[b], (int64_t)p->keep[b], w0}) + (n - w0);
   };
   // First pass: the total kept-chunk bound, which sizes the splits.
-  int64_t sel_total = 0, sel_most = 0;
+  int64_t sel_total = 0, sel_most = 0, all_chunks = 0;
   for (int b = 0; b < B; ++b) {
+    const int64_t L = std::max<int64_t>(p->ctx_tokens[b], 0);
+    all_chunks += L / C + (L % C != 0);
     sel_total += kept_bound(b);
     sel_most = std::max(sel_most, kept_bound(b));
   }
+  const int srows = score_rows_per_wg(p->emb_dtype, p->emb_dim, p->n_lookahead, all_chunks);
   const int tpc = C / 32;
   P.one_split = rows <= 16 && sel_most * tpc <= kOneSplitTiles;
   const int target = rows <= 16 && B <= kFewSequences ? kTargetWorkgroupsFew : kTargetWorkgroups;

@@ -170,7 +170,7 @@ hipError_t launch_score_select(const SeqTable& t, int32_t emb_dtype, int32_t emb
 // keys == true writes order keys instead of scores (for the fused step).
 hipError_t launch_score(const SeqTable& t, int32_t emb_dtype, int32_t emb_dim, const void* qe,
                         const void* E, void* scores, bool keys, hipStream_t s);
-int score_rows_per_wg(int32_t emb_dtype, int32_t emb_dim, int32_t n_lookahead);
+int score_rows_per_wg(int32_t emb_dtype, int32_t emb_dim, int32_t n_lookahead, int64_t total_chunks);
 
 // Selection variants.  recall: k_b becomes min(keep[b], number of keys >= the
 // key of +0.0), i.e. the entries whose sigmoid score reaches 1/2, bounded by

@@ -272,16 +272,19 @@ score_select_kernel(SeqTable t, const uint8_t* __restrict__ qe, const uint8_t* _
 // exactly once.  A lane's four scores of a group are four consecutive chunks of
 // one query and leave as one 16-byte store.
 constexpr int kMfmaMinQueries = 4;
-// 16-chunk groups per wave.  The groups share the wave's query operand, so the
-// query embeddings are read from L2 once per 16 x groups chunks: 4 groups up
-// to D = 256, 2 at D = 512 (4 groups of A operands would take 256 registers).
-template <int D> constexpr int mfma_groups() { return D >= 512 ? 2 : 4; }
-template <int D> constexpr int mfma_rows_per_wg() { return 4 * 16 * mfma_groups<D>(); }
+// 16-chunk groups per wave: the groups share the wave's query operand, so with
+// two the query embeddings are read from L2 half as often, which pays only
+// where the grid stays large.  65,536 chunks, 16 queries: 9.1 us with two, 10.1
+// with one, 9.7 with four; 13,300 chunks, 4 queries: 4.9, 4.8 and 7.0; 27,000
+// chunks, 8 queries: 7.2, 6.3 and 7.8.
+constexpr int64_t kMfmaTwoGroups = 32768;  // chunks in the call from which waves take two groups
+int mfma_groups(int64_t total_chunks) { return total_chunks >= kMfmaTwoGroups ? 2 : 1; }
+constexpr int mfma_rows_per_wg(int groups) { return 4 * 16 * groups; }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <int D, bool KEYS>
+template <int D, bool KEYS, int kGroups>
 __global__ void __launch_bounds__(kThreads)
 score_mfma_kernel(SeqTable t, const uint16_t* __restrict__ qe, const uint16_t* __restrict__ E,
                   uint32_t* __restrict__ scores) {
@@ -290,8 +293,7 @@ score_mfma_kernel(SeqTable t, const uint16_t* __restrict__ qe, const uint16_t* _
   const SeqData sq = seq_data(t, t.score_wg_off, wg);
   const int b = sq.b, n = sq.n, Q = t.n_lookahead;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kGroups = mfma_groups<D>();
-  const int c0 = (wg - sq.wg0) * mfma_rows_per_wg<D>() + wave * 16 * kGroups;
+  const int c0 = (wg - sq.wg0) * mfma_rows_per_wg(kGroups) + wave * 16 * kGroups;
   if (c0 >= n) return;
   // A operand rows: chunk c0 + 16 gi + lane % 16 (clamped; its scores are not stored)
   bf16x8 ea[kGroups][kSteps];
@@ -338,17 +340,24 @@ score_mfma_kernel(SeqTable t, const uint16_t* __restrict__ qe, const uint16_t* _
   zero_arrivals(t);  // wave 0 of workgroup 0 never returns early (c0 = 0)
 }
 
-template <int D>
-hipError_t launch_mfma_d(const SeqTable& t, const void* qe, const void* E, void* scores, bool keys, hipStream_t s) {
+template <int D, int GROUPS>
+hipError_t launch_mfma_g(const SeqTable& t, const void* qe, const void* E, void* scores, bool keys, hipStream_t s) {
   const int grid = t.score_wg_off[t.batch];
   const auto* q16 = static_cast<const uint16_t*>(qe);
   const auto* e16 = static_cast<const uint16_t*>(E);
   auto* out = static_cast<uint32_t*>(scores);
   if (keys)
-    hipLaunchKernelGGL((score_mfma_kernel<D, true>), dim3(grid), dim3(kThreads), 0, s, t, q16, e16, out);
+    hipLaunchKernelGGL((score_mfma_kernel<D, true, GROUPS>), dim3(grid), dim3(kThreads), 0, s, t, q16, e16, out);
   else
-    hipLaunchKernelGGL((score_mfma_kernel<D, false>), dim3(grid), dim3(kThreads), 0, s, t, q16, e16, out);
+    hipLaunchKernelGGL((score_mfma_kernel<D, false, GROUPS>), dim3(grid), dim3(kThreads), 0, s, t, q16, e16, out);
   return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_mfma_d(const SeqTable& t, const void* qe, const void* E, void* scores, bool keys, hipStream_t s) {
+  // (t was laid out with the same rule, score_rows_per_wg)
+  if (mfma_groups(t.chunk_off[t.batch]) == 2) return launch_mfma_g<D, 2>(t, qe, E, scores, keys, s);
+  return launch_mfma_g<D, 1>(t, qe, E, scores, keys, s);
 }
 
 bool use_mfma(int32_t emb_dtype, int32_t n_lookahead) {
@@ -409,16 +418,8 @@ int rows_dt(int32_t D) {
 
 }  // namespace
 
-int score_rows_per_wg(int32_t emb_dtype, int32_t emb_dim, int32_t n_lookahead) {
-  if (use_mfma(emb_dtype, n_lookahead)) {
-    switch (emb_dim) {
-      case 64: return mfma_rows_per_wg<64>();
-      case 128: return mfma_rows_per_wg<128>();
-      case 256: return mfma_rows_per_wg<256>();
-      case 512: return mfma_rows_per_wg<512>();
-      default: return 0;
-    }
-  }
+int score_rows_per_wg(int32_t emb_dtype, int32_t emb_dim, int32_t n_lookahead, int64_t total_chunks) {
+  if (use_mfma(emb_dtype, n_lookahead)) return mfma_rows_per_wg(mfma_groups(total_chunks));
   switch (emb_dtype) {
     case LSA_F32: return rows_dt<LSA_F32>(emb_dim);
     case LSA_BF16: return rows_dt<LSA_BF16>(emb_dim);
