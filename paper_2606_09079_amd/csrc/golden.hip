@@ -46,6 +46,7 @@
 // when the row kernel read every row three times; it takes 165 us now (scan 120,
 // rows 27, general path 4.5 with no row left to it, votes 9, labels 5), and about
 // 260 us for the one window in ten that leaves a row to the general path.
+#include "golden_geometry.h"
 #include "lsa_internal.h"
 
 namespace lsa {
@@ -60,8 +61,7 @@ constexpr int kSubPerThread = kSubBins / kThreads;
 constexpr int kCand = 1024;     // entries of the threshold bin staged in LDS
 constexpr int kUnroll = 16;     // 64-entry groups per wavefront per round
 constexpr int kScanVec = kGoldenSliceVecs / kThreads;  // float4s of a slice a thread holds
-constexpr int kSliceListMax = 340;    // entries a slice lists at most
-constexpr int kGoldenSlots = 3072;    // listed entries of a row the row kernel takes in
+static_assert(kThreads == kGoldenScanThreads, "scan geometry");
 
 struct u128 {
   uint64_t hi, lo;
@@ -138,19 +138,8 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_to
   return before + incl - v;
 }
 
-// What golden_scan_kernel leaves of a slice, in 32-bit words at the slice's
-// share of the row's bitmap: the maximum m (float), the threshold key, the sum
-// of the other entries' weights 2^(x c - m c) (float), the number of listed
-// entries, then `cap` values and `cap` 16-bit entry numbers within the slice.
-constexpr int kSliceHead = 4;
-constexpr float kLog2e = 1.44269502f;  // c
+constexpr float kLog2e = 1.44269502f;  // c of a slice's weights 2^(x c - m c)
 
-// Geometry of the ns slices of a row: the slice's words of the row's bitmap
-// and how many entries it can list, the same for every slice of a row.
-__device__ __forceinline__ int slice_words(int words, int ns) { return words / ns; }
-__device__ __forceinline__ int slice_cap(int words, int ns) {
-  return min((slice_words(words, ns) - kSliceHead) * 2 / 3, min(kGoldenSlots / ns, kSliceListMax));
-}
 // Scale of a slice's sum: weight of entry x is 2^(x c + off), off rounded to float32.
 __device__ __forceinline__ float slice_off(float m) { return m == -INFINITY ? 0.f : -(m * kLog2e); }
 
@@ -218,15 +207,14 @@ golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
   const int local = (int)(id - gt.scan_off[b]);
   const int row = local / ns, sl = local - row * ns;
   const int64_t first = gt.logit_off[b] + (int64_t)row * n;
-  const int lead = (int)(first & 3);  // the row starts `lead` entries into a float4
-  const int v0 = sl * vps, v1 = min(v0 + vps, (n + lead + 3) >> 2);
+  const auto [lead, v0, v1, have] = scan_slice(first, n, vps, sl);
   const float* p0 = a.logits + (first - lead) + 4 * (int64_t)v0;
 
   // float4 v holds entries 4 v - lead .. + 3 of the row; the last one of a row
   // may reach past its end and is read entry by entry.  The buffer ends with
   // the slice's whole float4s: loads past it return 0, which -inf replaces.
+  // (The whole offset is the vector offset, which the range check is defined on.)
   f32x4 x[kScanVec];
-  const int have = min(v1, (n + lead) / 4) - v0;
   {
     constexpr int kNontemporal = 2;  // the nt bit of a buffer instruction's cache policy
     const __amdgpu_buffer_rsrc_t src =
@@ -234,7 +222,7 @@ golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
 #pragma unroll
     for (int j = 0; j < kScanVec; ++j) {
       typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4 y = __builtin_amdgcn_raw_buffer_load_b128(src, 16 * tid, 16 * kThreads * j, kNontemporal);
+      const u32x4 y = __builtin_amdgcn_raw_buffer_load_b128(src, scan_offset(tid, j), 0, kNontemporal);
       x[j] = __builtin_bit_cast(f32x4, y);
     }
   }
@@ -371,9 +359,8 @@ __device__ __forceinline__ double slice_error(double m, double M, double R, doub
   return 1.4e-8 * fabs(m) + 1.5e-7 * d + 6e-8 * (M - m) + 1.1e-6;
 }
 
-// Mark of a scanned row that the row kernel leaves open, in a word of its
-// bitmap that holds a list entry of the first slice until then.
-constexpr int kOpenWord = kSliceHead;
+// Mark of a scanned row that the row kernel leaves open, in word kOpenWord of
+// its bitmap.
 constexpr uint32_t kOpenRow = 0x9E3779B9u;
 
 constexpr int kRowThreads = 256;
@@ -431,14 +418,12 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
     }
     kth = 1u;
   } else {
-    // slot f is entry f % cap of slice f / cap; the division by multiplication
-    // is exact for f < 2^16
-    const int cap = max(slice_cap(words, ns), 1);
-    const uint32_t inv = (uint32_t)((0xFFFFFFFFull + (uint32_t)cap) / (uint32_t)cap);
+    const int cap = slice_cap(words, ns);
+    const uint32_t inv = slot_inverse((uint32_t)cap);
     const int lead = (int)((gt.logit_off[b] + (int64_t)row * n) & 3);
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const uint32_t f = (uint32_t)(tid + j * kRowThreads), s = __umulhi(f, inv), i = f - s * (uint32_t)cap;
+      const uint32_t f = (uint32_t)(tid + j * kRowThreads), s = slot_slice(f, inv), i = f - s * (uint32_t)cap;
       uint32_t v = 0u, id = 0u, c = 0u;
       if ((int)s < ns) {
         const uint32_t* src = bm + (int64_t)s * sw;
@@ -447,7 +432,7 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
         id = reinterpret_cast<const uint16_t*>(src + kSliceHead + cap)[i];
       }
       key[j] = i < c ? key_of(__uint_as_float(v)) : 0u;
-      idx[j] = 4u * s * (uint32_t)vps + id - (uint32_t)lead;
+      idx[j] = slice_entry(s, vps, id, lead);
     }
     if (tid < ns) {
       const uint32_t* src = bm + (int64_t)tid * sw;

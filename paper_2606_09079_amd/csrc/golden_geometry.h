@@ -1,0 +1,76 @@
+// Index arithmetic of the golden-label scan as plain constexpr functions, which
+// the host's plan, the kernels and the CPU tests (built without HIP) share.
+#ifndef LSA_GOLDEN_GEOMETRY_H_
+#define LSA_GOLDEN_GEOMETRY_H_
+
+#include <stdint.h>
+
+namespace lsa {
+
+// The row kernel holds up to kGoldenListMax entries of a row; a longer row is
+// scanned first, in slices of up to kGoldenSliceVecs float4s (16,384 entries),
+// which leave their largest entries to it.
+constexpr int kGoldenListMax = 2048;
+constexpr int kGoldenSliceVecs = 4096;
+constexpr int kGoldenScanThreads = 512;
+constexpr int kSliceListMax = 340;  // entries a slice lists at most
+constexpr int kGoldenSlots = 3072;  // listed entries of a row the row kernel takes in
+
+// What the scan leaves of a slice, in 32-bit words at the slice's share of the
+// row's bitmap: the maximum m (float), the threshold key, the sum of the other
+// entries' weights 2^(x c - m c) (float), the number of listed entries, then
+// `cap` values and `cap` 16-bit entry numbers within the slice.
+constexpr int kSliceHead = 4;
+// Word of the row's bitmap that marks a scanned row the row kernel leaves open;
+// it holds a list entry of the first slice until then.
+constexpr int kOpenWord = kSliceHead;
+
+constexpr int least(int a, int b) { return a < b ? a : b; }
+
+// Slices of a row of n entries whose sequence starts at logit `first`, 0 where
+// the row kernel reads the whole row: slices of equal length in float4s; a row
+// that may start inside a float4 spans one more.
+struct GoldenSlices {
+  int32_t slices, slice_vecs;
+};
+constexpr GoldenSlices golden_slices(int64_t n, int64_t first) {
+  if (n <= kGoldenListMax) return {0, 0};
+  const int64_t vecs = n % 4 == 0 && first % 4 == 0 ? n / 4 : (n + 6) / 4;
+  const int64_t ns = (vecs + kGoldenSliceVecs - 1) / kGoldenSliceVecs;
+  return {(int32_t)ns, (int32_t)((vecs + ns - 1) / ns)};
+}
+
+// The slice's words of the row's bitmap and how many entries it can list, the
+// same for every slice of a row.
+constexpr int slice_words(int words, int ns) { return words / ns; }
+constexpr int slice_cap(int words, int ns) {
+  return least((slice_words(words, ns) - kSliceHead) * 2 / 3, least(kGoldenSlots / ns, kSliceListMax));
+}
+
+// Slice sl of the row that starts at logit `first`: float4 v of the row holds
+// its entries 4 v - lead .. + 3 and sits at logit first - lead + 4 v, a multiple
+// of 4; the slice takes float4s v0 .. v1 - 1, of which the first `have` lie
+// within the row (the next one, if any, reaches past its end).
+struct ScanSlice {
+  int lead, v0, v1, have;
+};
+constexpr ScanSlice scan_slice(int64_t first, int n, int slice_vecs, int sl) {
+  const int lead = (int)(first & 3), v0 = sl * slice_vecs;
+  const int v1 = least(v0 + slice_vecs, (n + lead + 3) >> 2);
+  return {lead, v0, v1, least(v1, (n + lead) / 4) - v0};
+}
+// Byte offset within the slice of float4 j of thread tid.
+constexpr int scan_offset(int tid, int j) { return 16 * (tid + kGoldenScanThreads * j); }
+
+// Slot f of a row kernel's list is entry f % cap of slice f / cap; the division
+// by multiplication is exact for f < 2^16.
+constexpr uint32_t slot_inverse(uint32_t cap) { return (0xFFFFFFFFu + (uint64_t)cap) / cap; }
+constexpr uint32_t slot_slice(uint32_t f, uint32_t inverse) { return (uint32_t)(((uint64_t)f * inverse) >> 32); }
+// Entry of the row that entry `id` of slice s stands for.
+constexpr uint32_t slice_entry(uint32_t s, int slice_vecs, uint32_t id, int lead) {
+  return 4u * s * (uint32_t)slice_vecs + id - (uint32_t)lead;
+}
+
+}  // namespace lsa
+
+#endif  // LSA_GOLDEN_GEOMETRY_H_

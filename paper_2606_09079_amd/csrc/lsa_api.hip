@@ -9,6 +9,7 @@
 #include <cmath>
 #include <mutex>
 
+#include "golden_geometry.h"
 #include "lsa_internal.h"
 
 namespace lsa {
@@ -503,16 +504,12 @@ lsa_status make_golden_plan(const lsa_golden* g, GoldenPlan* gp) {
     t.logit_off[b] = rows * entries;
     t.bit_off[b] = bits;
     t.label_word_off[b] = labels;
-    // rows longer than the row kernel holds are scanned in slices of equal
-    // length; a row that does not start on a float4 spans one float4 more
+    // rows longer than the row kernel holds are scanned in slices
+    const GoldenSlices gs = golden_slices(n, t.logit_off[b]);
     t.scan_off[b] = scans;
-    if (n > kGoldenListMax) {
-      const bool aligned = n % 4 == 0 && t.logit_off[b] % 4 == 0;
-      const int64_t vecs = aligned ? n / 4 : (n + 6) / 4;
-      t.slices[b] = (int32_t)((vecs + kGoldenSliceVecs - 1) / kGoldenSliceVecs);
-      t.slice_vecs[b] = (int32_t)((vecs + t.slices[b] - 1) / t.slices[b]);
-      scans += rows * t.slices[b];
-    }
+    t.slices[b] = gs.slices;
+    t.slice_vecs[b] = gs.slice_vecs;
+    scans += rows * gs.slices;
     entries += n;
     bits += rows * t.words[b];
     labels += t.words[b];

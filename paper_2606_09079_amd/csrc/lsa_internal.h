@@ -303,11 +303,6 @@ hipError_t launch_tier_fetch(const SeqTable& t, const TierFetchArgs& a, int32_t 
 hipError_t launch_tier_reset(int32_t* owner, int64_t n, hipStream_t s);
 
 // Golden-label pipeline: per-sequence geometry (by value) and launch arguments.
-// The row kernel holds up to kGoldenListMax entries of a row; a longer row is
-// scanned first, in slices of up to kGoldenSliceVecs float4s (16,384 entries),
-// which leave their largest entries to it.
-constexpr int kGoldenListMax = 2048;
-constexpr int kGoldenSliceVecs = 4096;
 struct GoldenTable {
   int32_t batch;
   int32_t n[LSA_MAX_BATCH];                // entries n_b
