@@ -77,6 +77,8 @@ def bind(path: str) -> ctypes.CDLL:
     L.oracle_two_level.restype = _I64
     L.oracle_top_p.argtypes = [_P, _I64, _I64, _I64, _P, _P, _P]
     L.oracle_top_p.restype = _I64
+    L.oracle_top_p_fixed.argtypes = [_P, _I64, _I64, _I64, _P, _P]
+    L.oracle_top_p_fixed.restype = _I64
     L.oracle_golden_labels.argtypes = [_P, _I32, _I32, _I64, _I64, _I64, _I32, _P, _P, _P]
     L.oracle_golden_labels.restype = _I64
     return L
@@ -323,6 +325,20 @@ def top_p(S: np.ndarray, p_num: int, p_den: int, detail: bool = False):
     if size < 0:
         raise ValueError("oracle_top_p rejected its arguments")
     return (mark, int(size), order, cum) if detail else (mark, int(size))
+
+
+def top_p_fixed(S: np.ndarray, p_num: int, p_den: int, detail: bool = False):
+    """Top-p set of one row by the contract's integer decision (fixed float32
+    exponential, masses in units of 2^-40): (0/1 marks [n], set size), plus,
+    with ``detail``, the cumulative integer mass of every prefix."""
+    S = _c(S, np.float32)
+    mark = np.zeros(len(S), dtype=np.uint8)
+    mass = np.empty(len(S), dtype=np.uint64) if detail else None
+    size = lib().oracle_top_p_fixed(S.ctypes.data, len(S), p_num, p_den, mark.ctypes.data,
+                                    mass.ctypes.data if detail else None)
+    if size < 0:
+        raise ValueError("oracle_top_p_fixed rejected its arguments")
+    return (mark, int(size), mass) if detail else (mark, int(size))
 
 
 def golden_labels(logits: np.ndarray, p_num: int, p_den: int, theta: int):

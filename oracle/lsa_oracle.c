@@ -420,6 +420,63 @@ int64_t oracle_top_p(const float* S, int64_t n, int64_t p_num, int64_t p_den, ui
   return size;
 }
 
+/* exp(x), x <= 0, by the one float32 method that the library's contract fixes:
+ * Cody-Waite reduction, Taylor series of degree 7 with fused multiply-adds, 0
+ * below -64. */
+static float fixed_exp(float x) {
+  if (x < -64.0f) return 0.0f;
+  const float k = rintf(x * 1.44269502e+00f);
+  float r = fmaf(-k, 6.9314575195e-01f, x);
+  r = fmaf(-k, 1.4286067653e-06f, r);
+  float p = 1.0f / 5040.0f;
+  p = fmaf(p, r, 1.0f / 720.0f);
+  p = fmaf(p, r, 1.0f / 120.0f);
+  p = fmaf(p, r, 1.0f / 24.0f);
+  p = fmaf(p, r, 1.0f / 6.0f);
+  p = fmaf(p, r, 1.0f / 2.0f);
+  p = fmaf(p, r, 1.0f);
+  p = fmaf(p, r, 1.0f);
+  return ldexpf(p, (int)k);
+}
+
+/*
+ * The same set by the integer decision of the contract: entry s weighs
+ * q_s = floor(fixed_exp(S_s - max S) 2^40), and the set is the shortest prefix
+ * of the order above whose mass times p_den reaches p_num times the total
+ * mass.  Unlike oracle_top_p this fixes every bit.  mass (nullable) receives
+ * the cumulative mass of every prefix.
+ */
+int64_t oracle_top_p_fixed(const float* S, int64_t n, int64_t p_num, int64_t p_den, uint8_t* mark, uint64_t* mass) {
+  if (n < 1 || p_num < 1 || p_den < p_num) return -1;
+  float m = S[0];
+  for (int64_t s = 1; s < n; ++s)
+    if (S[s] > m) m = S[s];
+  logit_entry* v = (logit_entry*)malloc((size_t)n * sizeof *v);
+  if (!v) return -1;
+  uint64_t total = 0;
+  for (int64_t s = 0; s < n; ++s) {
+    v[s].s = S[s];
+    v[s].c = s;
+    const float x = S[s] - m;
+    total += (uint64_t)ldexp((double)fixed_exp(x), 40);
+  }
+  qsort(v, (size_t)n, sizeof *v, by_logit_desc);
+  memset(mark, 0, (size_t)n);
+  uint64_t head = 0;
+  int64_t size = -1;
+  for (int64_t j = 0; j < n; ++j) {
+    const float x = v[j].s - m;
+    head += (uint64_t)ldexp((double)fixed_exp(x), 40);
+    if (mass) mass[j] = head;
+    if (size < 0) {
+      mark[v[j].c] = 1;
+      if ((unsigned __int128)head * (uint64_t)p_den >= (unsigned __int128)total * (uint64_t)p_num) size = j + 1;
+    }
+  }
+  free(v);
+  return size;
+}
+
 /*
  * The label pipeline of one window: logits [tau][L][n] (row (i, l) holds
  * S_{i,l,.}).  For each step i the top-p set of every layer, the vote count

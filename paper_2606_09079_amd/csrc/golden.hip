@@ -138,11 +138,6 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_to
   return before + incl - v;
 }
 
-constexpr float kLog2e = 1.44269502f;  // c of a slice's weights 2^(x c - m c)
-
-// Scale of a slice's sum: weight of entry x is 2^(x c + off), off rounded to float32.
-__device__ __forceinline__ float slice_off(float m) { return m == -INFINITY ? 0.f : -(m * kLog2e); }
-
 __device__ __forceinline__ float max3(float a, float b, float c) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -318,7 +313,7 @@ golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
   for (int j = 0; j < kScanVec; ++j) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(x[j][i], kLog2e, off));
+      const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(x[j][i], kSliceLog2e, off));
       acc[i] += x[j][i] >= th ? 0.f : w;
     }
   }
@@ -341,22 +336,6 @@ golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
     dst[2] = __float_as_uint((float)s);
     dst[3] = count;
   }
-}
-
-// How far a slice's sum R of n weights e^-d (d: the distance below the slice's
-// maximum m; M is the row's) may be from the exact masses of the same entries,
-// relative to R, beyond which the exact masses only lose their floor.  Entry by
-// entry the errors are at most
-//   1.34e-8 |x|            c against log2 e (|x| <= |m| + d), in the exponent
-//   6e-8 d                 the rounding of the exponent, at most d / log 2 in size
-//   2.4e-7                 the hardware's exponential
-//   5.4e-7                 nine roundings of the float32 sums
-//   6e-8 (d + M - m + 4)   the exact method itself
-// and the mean of d over the weights is at most log(n / R), its value when all
-// of them are equal.  (Entries further than 87 below m have no weight.)
-__device__ __forceinline__ double slice_error(double m, double M, double R, double n) {
-  const double d = fmax(log(n / R), 0.0);
-  return 1.4e-8 * fabs(m) + 1.5e-7 * d + 6e-8 * (M - m) + 1.1e-6;
 }
 
 // Mark of a scanned row that the row kernel leaves open, in word kOpenWord of
@@ -487,11 +466,13 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
   }
   double rest = 0.0, err = 0.0;
   auto add_slice = [&](float hm_, float hsum_) {
-    if (hsum_ <= 0.f) return;  // (not so for NaN)
+    // no sum where no entry is left (not so for NaN, nor where the scale's own
+    // rounding may have made every weight underflow: that leaves the row open)
+    if (hsum_ <= 0.f && slice_error((double)hm_, (double)m, 0.0) < 1.0) return;
     // the weights' scale is 2^off, not the maximum
     const double R = (double)hsum_ * exp(-(double)slice_off(hm_) * 0.69314718055994530942 - (double)m);
     rest += R;
-    err += R * slice_error((double)hm_, (double)m, (double)hsum_, (double)(4 * vps));
+    err += R * slice_error((double)hm_, (double)m, fmax(log((double)(4 * vps) / (double)hsum_), 0.0));
   };
   if (tid < ns) add_slice(hm, hsum);
   for (int s = tid + kRowThreads; s < ns; s += kRowThreads)

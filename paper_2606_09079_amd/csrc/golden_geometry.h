@@ -71,6 +71,29 @@ constexpr uint32_t slice_entry(uint32_t s, int slice_vecs, uint32_t id, int lead
   return 4u * s * (uint32_t)slice_vecs + id - (uint32_t)lead;
 }
 
+// Scale of a slice's sum: the weight of entry x is 2^(x c + off) with c =
+// kSliceLog2e and off = -m c, each rounded to float32 (m: the slice's maximum).
+constexpr float kSliceLog2e = 1.44269502f;
+constexpr float slice_off(float m) { return m == -__builtin_inff() ? 0.f : -(m * kSliceLog2e); }
+
+// How far a slice's sum R of n weights e^-d (d: the distance below the slice's
+// maximum m; M is the row's) may be from the exact masses of the same entries,
+// relative to R, beyond which the exact masses only lose their floor.  Entry by
+// entry the errors are at most
+//   1.34e-8 |x|            c against log2 e (|x| <= |m| + d), in the exponent
+//   6e-8 d                 the rounding of the exponent, at most d / log 2 in size
+//   2.4e-7                 the hardware's exponential
+//   5.4e-7                 nine roundings of the float32 sums
+//   6e-8 (d + M - m + 4)   the exact method itself
+// and the mean of d over the weights is at most mean_d = log(n / R), its value
+// when all of them are equal.  (Entries further than 87 below m have no weight.)
+// The first is an error e of the exponent, a factor of up to exp(e) <= 1 + e + e^2
+// for e < 1; logits of 10^7 reach 0.14, and past e = 1 the sum says nothing.
+constexpr double slice_error(double m, double M, double mean_d) {
+  const double e = 1.4e-8 * (m < 0.0 ? -m : m) + 1.5e-7 * mean_d + 6e-8 * (M - m) + 1.1e-6;
+  return e < 1.0 ? e + e * e : __builtin_inf();
+}
+
 }  // namespace lsa
 
 #endif  // LSA_GOLDEN_GEOMETRY_H_

@@ -20,6 +20,6 @@ def _run(tmp_path, source):
     assert res.returncode == 0 and res.stdout.startswith("ok"), res.stdout[-2000:] + res.stderr[-2000:]
 
 
-@pytest.mark.parametrize("source", ["golden_geometry_check.cpp"])
+@pytest.mark.parametrize("source", ["golden_geometry_check.cpp", "golden_interval_check.cpp"])
 def test_golden_host_arithmetic(tmp_path, source):
     _run(tmp_path, source)

@@ -1,0 +1,64 @@
+"""Top-p sets bit for bit: the contract's decision is one of integers (masses in
+units of 2^-40 from one fixed float32 exponential), so every row's set and size
+must equal those of the oracle's integer decision, whichever kernel decided the
+row.  Rows whose remainder is only known as an interval are tried with p just
+inside and just outside of it, down to one part in 2^30, and with logits so
+large that the interval has to widen.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def run_rows(rows, p_num, p_den):
+    """One call, one step, the rows [L][n] as its layers: (marks [L][n], sizes [L])."""
+    import torch
+    import paper_2606_09079_amd as L_
+    L, n = rows.shape
+    g = L_.Golden([n], 1, L, 1, p_num, p_den)
+    wsb = L_.lsa_golden_sizes(g)
+    x = torch.from_numpy(np.ascontiguousarray(rows).reshape(-1)).cuda()
+    ws = torch.zeros(wsb, dtype=torch.uint8, device="cuda")
+    labels = torch.zeros(n, dtype=torch.int32, device="cuda")
+    count = torch.zeros(1, dtype=torch.int32, device="cuda")
+    sizes = torch.zeros(1, 1, L, dtype=torch.int32, device="cuda")
+    L_.lsa_golden_labels(g, x, labels, count, sizes, None, ws, wsb)
+    torch.cuda.synchronize()
+    words = (n + 31) // 32
+    bits = ws.cpu().numpy()[:L * words * 4].reshape(L, words * 4)
+    return np.unpackbits(bits, axis=1, bitorder="little")[:, :n], sizes.cpu().numpy()[0, 0]
+
+
+def check_exact(rows, p_num, p_den, where):
+    marks, sizes = run_rows(rows, p_num, p_den)
+    for l in range(rows.shape[0]):
+        want, size = oracle.top_p_fixed(rows[l], p_num, p_den)
+        assert sizes[l] == size, f"{where} layer {l}: size {sizes[l]}, exact {size}"
+        assert np.array_equal(marks[l], want), f"{where} layer {l}: another set of {size} entries"
+
+
+def _two_levels(n, top, mag, gap):
+    """`top` entries at mag spread over the row, all others one float below at mag - gap."""
+    x = np.full(n, np.float32(mag) - np.float32(gap), np.float32)
+    x[np.arange(top) * (n // top) + 3] = np.float32(mag)
+    return x
+
+
+@pytest.mark.parametrize("n", [32768, 40003])
+@pytest.mark.parametrize("mag,gap", [(1e6, 4.0), (1e7, 4.0), (2e7, 6.0), (1e8, 8.0), (-1e7, 4.0), (-1e8, 8.0)])
+def test_golden_exact_large_logits(n, mag, gap):
+    """A remainder of equal entries `gap` below 256 large equal maxima: the
+    scan's weights are off by exp(1.3e-8 mag), and p lies where the true
+    remainder asks for one entry more than the scan's own sum would."""
+    row = _two_levels(n, 256, mag, gap)
+    _, _, mass = oracle.top_p_fixed(row, 1, 1, detail=True)
+    Z, top = float(mass[-1]), float(mass[0])
+    for k in (1, 2, 7, 100):
+        for side in (-3e-3, -1e-6, 1e-6, 3e-3):  # just under and over k entries
+            p = int(round(k * top / Z * (1.0 + side) * 2 ** 30))
+            check_exact(row[None], p, 2 ** 30, f"n={n} mag={mag} k={k} side={side}")
