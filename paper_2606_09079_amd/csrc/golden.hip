@@ -305,7 +305,8 @@ golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
       before += w < wave ? c : 0u;
       count += c;
     }
-    if (count <= (uint32_t)max(cap, 0)) break;  // uniform; always at level 5, which lists nothing
+    if (count <= (uint32_t)cap) break;  // uniform; always at level 5, which lists nothing
+    if (th == m) level = 4;  // every further threshold is m too (a slice of equal entries, masked ones for example)
     lds_barrier();
   }
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -466,6 +467,7 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
   }
   double rest = 0.0, err = 0.0;
   auto add_slice = [&](float hm_, float hsum_) {
+    if (slice_weightless((double)hm_, (double)m)) return;
     // no sum where no entry is left (not so for NaN, nor where the scale's own
     // rounding may have made every weight underflow: that leaves the row open)
     if (hsum_ <= 0.f && slice_error((double)hm_, (double)m, 0.0) < 1.0) return;

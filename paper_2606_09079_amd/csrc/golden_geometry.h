@@ -94,6 +94,12 @@ constexpr double slice_error(double m, double M, double mean_d) {
   return e < 1.0 ? e + e * e : __builtin_inf();
 }
 
+// Whether no entry of a slice has any mass: every one lies more than 64 below
+// the row's maximum M, where the fixed exponential is 0 (as are the masses from
+// 27.8 on).  Slices masked with a large negative number, the type's lowest one
+// among them, whose sum may be infinite or not a number.
+constexpr bool slice_weightless(double m, double M) { return M - m > 64.0; }
+
 }  // namespace lsa
 
 #endif  // LSA_GOLDEN_GEOMETRY_H_

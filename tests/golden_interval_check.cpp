@@ -77,6 +77,20 @@ int main() {
               }
             }
           }
+  // slices that lie so far below the row's maximum that they are left out have no mass
+  const float lowest = -3.402823466e38f;
+  for (float M : {-1e30f, -1e9f, -100.f, 0.f, 5.f, 1e9f, 3e38f})
+    for (double below : {64.0 + 1e-5, 65.0, 1e4, 1e10, 1e30, 3.4e38}) {
+      const double md = (double)M - below;
+      const float m = md < (double)lowest ? lowest : (float)md;
+      if (!slice_weightless((double)m, (double)M)) continue;
+      ++tried;
+      if (fixed_exp(m - M) * 0x1p40f >= 1.f) {
+        printf("m=%g M=%g: an entry of a weightless slice has mass\n", (double)m, (double)M);
+        return 1;
+      }
+    }
+  if (!slice_weightless((double)lowest, -1e30) || slice_weightless(-64.0, 0.0)) return 1;
   printf("ok: %ld slices, largest error %.3f of its bound\n", tried, worst);
   return 0;
 }
