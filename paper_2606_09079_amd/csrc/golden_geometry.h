@@ -7,9 +7,18 @@
 
 namespace lsa {
 
-// The row kernel holds up to kGoldenListMax entries of a row; a longer row is
-// scanned first, in slices of up to kGoldenSliceVecs float4s (16,384 entries),
-// which leave their largest entries to it.
+// Rows of up to kGoldenDirectMax entries are held in one workgroup's registers
+// (kGoldenHeld per thread) and decided there.  A longer row is scanned first, in
+// slices of up to kGoldenSliceVecs float4s (16,384 entries), which leave their
+// largest entries to the row kernel: up to kGoldenListMax candidates.  1,344
+// rows, us a call, peaked / flat logits, held against scanned: 2,500 entries
+// 29 / 33, 54 / 79; 8,192 36 / 52, 39 / 91; 16,384 48 / 74, 45 / 116; with 48
+// entries per thread (two workgroups per CU) 24,000 75 / 112, 56 / 134.  Past
+// 16,384 peaked rows lose more held than flat ones gain; flat rows of 16,385 to
+// 28,000 entries take 4 to 17% longer than three passes over them took (100, 125
+// us at 16,385 and 24,000), from 32,768 on less.
+constexpr int kGoldenHeld = 32;
+constexpr int kGoldenDirectMax = 512 * kGoldenHeld;
 constexpr int kGoldenListMax = 2048;
 constexpr int kGoldenSliceVecs = 4096;
 constexpr int kGoldenScanThreads = 512;
@@ -28,13 +37,13 @@ constexpr int kOpenWord = kSliceHead;
 constexpr int least(int a, int b) { return a < b ? a : b; }
 
 // Slices of a row of n entries whose sequence starts at logit `first`, 0 where
-// the row kernel reads the whole row: slices of equal length in float4s; a row
+// the exact kernel takes the whole row: slices of equal length in float4s; a row
 // that may start inside a float4 spans one more.
 struct GoldenSlices {
   int32_t slices, slice_vecs;
 };
 constexpr GoldenSlices golden_slices(int64_t n, int64_t first) {
-  if (n <= kGoldenListMax) return {0, 0};
+  if (n <= kGoldenDirectMax) return {0, 0};
   const int64_t vecs = n % 4 == 0 && first % 4 == 0 ? n / 4 : (n + 6) / 4;
   const int64_t ns = (vecs + kGoldenSliceVecs - 1) / kGoldenSliceVecs;
   return {(int32_t)ns, (int32_t)((vecs + ns - 1) / ns)};

@@ -311,7 +311,7 @@ struct GoldenTable {
   int64_t logit_off[LSA_MAX_BATCH];        // first logit of sequence b, tau * L * entry_off[b]
   int64_t bit_off[LSA_MAX_BATCH];          // first word of sequence b's row bitmaps
   int64_t label_word_off[LSA_MAX_BATCH];   // first word of sequence b's label bitmap
-  int32_t slices[LSA_MAX_BATCH];           // slices a row is scanned in, 0: the row kernel reads the whole row
+  int32_t slices[LSA_MAX_BATCH];           // slices a row is scanned in, 0: the exact kernel takes the whole row
   int32_t slice_vecs[LSA_MAX_BATCH];       // float4s per slice
   int64_t scan_off[LSA_MAX_BATCH + 1];     // first scan workgroup of sequence b, one per (row, slice)
 };
@@ -319,7 +319,7 @@ struct GoldenArgs {
   const float* logits;
   uint32_t* bits;          // [sum_b tau * L * words_b] top-p membership per row
   int32_t* nucleus_size;   // nullable [B][tau][L]
-  uint32_t* label_bits = nullptr;    // [label_words] zeroed by the row kernel's first workgroup
+  uint32_t* label_bits = nullptr;    // [label_words] zeroed by the first launch of one workgroup per row
   int64_t label_words = 0;
   int32_t* golden_count = nullptr;   // nullable [B][tau], zeroed likewise
   int64_t p_num, p_den;

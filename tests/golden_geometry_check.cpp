@@ -86,8 +86,8 @@ int main() {
     check_row(n, seq_first, seq_first + (n_rows - 1) * n, total, every_load);
   };
   // every length up to five slices, at every start within a float4
-  for (int64_t n = kGoldenListMax + 1; n <= 5 * 16384 + 70; n += n < 20000 ? 1 : 13)
-    for (int64_t first = 0; first < 4; ++first) sequence(n, first, 5, first + 5 * n, n < 2200 || n % 509 == 0);
+  for (int64_t n = kGoldenDirectMax + 1; n <= 5 * 16384 + 70; n += n < 17000 ? 1 : 13)
+    for (int64_t first = 0; first < 4; ++first) sequence(n, first, 5, first + 5 * n, n < 16500 || n % 509 == 0);
   // lengths around every whole number of slices, up to the longest
   for (int64_t k = 1; k <= 256; ++k)
     for (int64_t d = -9; d <= 9; ++d) {

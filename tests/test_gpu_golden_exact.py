@@ -42,6 +42,36 @@ def check_exact(rows, p_num, p_den, where):
         assert np.array_equal(marks[l], want), f"{where} layer {l}: another set of {size} entries"
 
 
+def _row(rng, L, n, kind):
+    x = rng.standard_normal((L, n)).astype(np.float32)
+    if kind == "peaked":  # 1 in 256 entries far above
+        x[:, rng.choice(n, size=max(1, n // 256), replace=False)] += np.float32(8.5)
+    elif kind == "wide":  # spread over every mass from 1 to 2^40 and to none
+        x *= np.float32(12.0)
+    elif kind == "grid":  # many equal logits
+        x = (np.round(x * 2.0) / 2.0).astype(np.float32)
+    elif kind == "masked":  # the second half at the type's lowest value
+        x[:, n // 2:] = np.finfo(np.float32).min
+    elif kind == "narrow":  # one histogram bin holds nearly all
+        x = (np.float32(1.0) + x * np.float32(0.01)).astype(np.float32)
+    return x  # "flat": as drawn
+
+
+# around the held sizes (8 and 32 entries per thread of 512), the candidates
+# that the threshold bin stages, one slice and several
+SIZES = [1, 2, 63, 64, 65, 511, 513, 1000, 2048, 4095, 4096, 4097, 5003, 8191, 8193, 12000, 16383, 16384, 16385, 16387,
+         32769, 50001, 131071]
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("kind", ["flat", "peaked", "wide", "grid", "masked", "narrow"])
+def test_golden_exact_rows(n, kind):
+    rng = np.random.default_rng(n * 7 + len(kind))
+    rows = _row(rng, 3, n, kind)
+    for p in ((3, 5), (1, 1000), (999, 1000), (1, 1)):
+        check_exact(rows, p[0], p[1], f"n={n} {kind} p={p}")
+
+
 def _two_levels(n, top, mag, gap):
     """`top` entries at mag spread over the row, all others one float below at mag - gap."""
     x = np.full(n, np.float32(mag) - np.float32(gap), np.float32)

@@ -1,8 +1,8 @@
-"""Golden-label rows that are scanned in slices before they are decided, at the
-sizes where the scan and the row kernel change what they do: rows that fit the
-row kernel, one slice, a slice boundary, rows that start inside a float4 (odd
-lengths), the largest entries in one slice, slices masked with the type's
-lowest value, many equal logits, and flat rows that the general path decides.
+"""Golden-label rows at the sizes where the kernels change what they do: rows
+held in registers (up to 16,384 entries), rows scanned in slices, a slice
+boundary, rows that start inside a float4 (odd lengths), the largest entries in
+one slice, slices masked with the type's lowest value, many equal logits, and
+flat rows that the exact kernel decides after the scan.
 Same oracle, band and exact follow-ups as the other golden-label tests.
 """
 from __future__ import annotations
