@@ -196,7 +196,7 @@ __device__ __forceinline__ void lds_barrier() {
 // (short slices, many equal logits) 16, 8, 4 or 2 groups raise it, and past
 // those nothing is listed and the threshold lies above the slice's maximum.
 __global__ void __launch_bounds__(kThreads, 8)
-golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
+golden_scan_kernel(GoldenTable gt, GoldenArgs a, int64_t first_slice) {
   __shared__ float list_x[kWaves][kSliceListMax];
   __shared__ uint16_t list_i[kWaves][kSliceListMax];
   __shared__ float group_max[32];
@@ -205,13 +205,13 @@ golden_scan_kernel(GoldenTable gt, GoldenArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int id = blockIdx.x;
+  const int64_t id = first_slice + blockIdx.x;
   // sequence of this slice: the last b whose first slice is not past it
   int b = 0;
   for (int step = 32; step > 0; step >>= 1)
-    if (b + step < gt.batch && gt.scan_off[b + step] <= (int64_t)id) b += step;
+    if (b + step < gt.batch && gt.scan_off[b + step] <= id) b += step;
   const int ns = gt.slices[b], n = gt.n[b], words = gt.words[b], vps = gt.slice_vecs[b];
-  const int local = (int)(id - gt.scan_off[b]);
+  const int local = (int)(id - gt.scan_off[b]);  // 2^31 slices of a sequence would be 70 TB of logits
   const int row = local / ns, sl = local - row * ns;
   const int64_t first = gt.logit_off[b] + (int64_t)row * n;
   const auto [lead, v0, v1, have] = scan_slice(first, n, vps, sl);
@@ -1118,8 +1118,10 @@ hipError_t launch_golden(const GoldenTable& gt, const GoldenArgs& a, uint32_t* l
   ra.label_bits = label_bits;
   ra.label_words = label_words;
   ra.golden_count = golden_count;
-  if (gt.scan_off[gt.batch] > 0)
-    hipLaunchKernelGGL(golden_scan_kernel, dim3((unsigned)gt.scan_off[gt.batch]), dim3(kThreads), 0, s, gt, ra);
+  // a grid holds fewer than 2^32 threads
+  for (int64_t first = 0; first < gt.scan_off[gt.batch]; first += kGoldenScanGrid)
+    hipLaunchKernelGGL(golden_scan_kernel, dim3((unsigned)std::min<int64_t>(kGoldenScanGrid, gt.scan_off[gt.batch] - first)),
+                       dim3(kThreads), 0, s, gt, ra, first);
   const dim3 rows((unsigned)(gt.batch * a.tau * a.layers));
   if (gt.scan_off[gt.batch] > 0) hipLaunchKernelGGL(golden_row_kernel, rows, dim3(kRowThreads), 0, s, gt, ra);
   hipLaunchKernelGGL(golden_exact_kernel, rows, dim3(kThreads), 0, s, gt, ra);

@@ -22,6 +22,8 @@ constexpr int kGoldenDirectMax = 512 * kGoldenHeld;
 constexpr int kGoldenListMax = 2048;
 constexpr int kGoldenSliceVecs = 4096;
 constexpr int kGoldenScanThreads = 512;
+constexpr int64_t kGoldenScanGrid = 1 << 22;  // slices of one launch
+static_assert(kGoldenScanGrid * kGoldenScanThreads < (int64_t(1) << 32), "threads of a grid");
 constexpr int kSliceListMax = 340;  // entries a slice lists at most
 constexpr int kGoldenSlots = 3072;  // listed entries of a row the row kernel takes in
 

@@ -1205,8 +1205,6 @@ lsa_status lsa_golden_labels(const lsa_golden* g, const float* logits, int32_t* 
   if (ws_bytes < G.ws_total)
     return fail(LSA_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, G.ws_total);
   if (ws == nullptr || !aligned16(ws)) return fail(LSA_ERR_WORKSPACE, "workspace is NULL or not 16-byte aligned");
-  if (G.t.scan_off[g->batch] > INT32_MAX)  // (logits past any GPU's memory)
-    return fail(LSA_ERR_UNSUPPORTED, "too many row slices for one launch");
   GoldenArgs a;
   a.logits = logits;
   a.bits = reinterpret_cast<uint32_t*>(at(ws, G.off_bits));
