@@ -42,6 +42,7 @@ struct Plan {
   int32_t group = 0, rows = 0, rows_pad = 16;
   int64_t chunk_stride = 0, head_stride = 0;
   int64_t n_units = 0;
+  bool equal_splits = false;
   bool one_split = false;  // every (b, g) in one workgroup that writes the output
   size_t emb_elem = 0;
   // two-level path: history chunks (before the window) per sequence, and the
@@ -58,7 +59,8 @@ struct Plan {
 // the kept set of sequence b is at most min(core_keep, keep, history) chunks
 // plus the window.
 // partial: contexts may end inside a chunk (attention alone).
-lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = nullptr, bool partial = false) {
+// equal: batches may be split into equal splits (up to twice as many partials).
+lsa_status plan_splits(const lsa_problem* p, Plan* pl, const lsa_two_level* tl, bool partial, bool equal) {
   if (p == nullptr) return fail(LSA_ERR_INVALID_ARG, "problem is NULL");
   const int B = p->batch;
   if (B < 1 || B > LSA_MAX_BATCH) return fail(LSA_ERR_INVALID_ARG, "batch %d not in [1, %d]", B, LSA_MAX_BATCH);
@@ -134,7 +136,7 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
   // round to whole ones, so some hold half as much again as others; equal
   // ones, at twice the number, leave the dispatcher something to balance.
   int64_t split_tiles = 0;
-  if (rows <= 16 && B > kFewSequences && !P.one_split &&
+  if (equal && rows <= 16 && B > kFewSequences && !P.one_split &&
       sel_total * tpc * p->n_kv_heads >= (int64_t)kBatchWorkgroups * kBatchTiles) {
     int64_t lo = 1, hi = std::max<int64_t>(sel_most * tpc, 1);
     while (lo < hi) {
@@ -146,6 +148,7 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
       else lo = mid + 1;
     }
     split_tiles = lo;
+    P.equal_splits = true;
   }
   int64_t chunk_off = 0, wg_off = 0, swg_off = 0;
   for (int b = 0; b < B; ++b) {
@@ -243,6 +246,18 @@ lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = n
   off = align_up(off + (size_t)B * p->n_kv_heads * 4);
   P.ws_total = off;
   return LSA_OK;
+}
+
+// A step whose workspace fits the library's scratch only with the fewer splits
+// takes those, so that the allocation-free call serves it (and every call plans
+// it alike).
+lsa_status make_plan(const lsa_problem* p, Plan* pl, const lsa_two_level* tl = nullptr, bool partial = false) {
+  const lsa_status st = plan_splits(p, pl, tl, partial, true);
+  if (st != LSA_OK || !pl->equal_splits || pl->ws_total <= LSA_SCRATCH_BYTES) return st;
+  Plan fewer;
+  const lsa_status sf = plan_splits(p, &fewer, tl, partial, false);
+  if (sf == LSA_OK && fewer.ws_total <= LSA_SCRATCH_BYTES) *pl = fewer;
+  return st;
 }
 
 lsa_status check_ptr(const void* ptr, const char* name) {

@@ -337,6 +337,22 @@ def test_noalloc_rejects_a_step_beyond_its_scratch():
                                          None) == B.LSA_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("chunks", [54000, 56500, 58000])
+def test_noalloc_serves_batches_whose_workspace_fits_with_one_round_of_splits(chunks):
+    """16 sequences of up to 3.7 million tokens with 16 lookahead queries: with
+    one resident round of splits (512 workgroups) the workspace is just below
+    64 MiB, and more splits must not push the step out of the scratch."""
+    k = chunks // 100
+    p = L.Problem([64 * chunks] * 16, 64, [k] * 16, 32, 8, n_lookahead=16)
+    parts = 512 * 16 * (128 + 2) * 4  # 512 splits, 16 rows: out, m and l
+    rest = 16 * 16 * chunks * 4 + 16 * min(16 * k, chunks) * 4 + 16 * 16 * k * 4 + 4096
+    assert parts + rest < 64 << 20
+    assert L.lsa_workspace_size(p) <= 64 << 20
+    rc = L.LIB.lsa_decode_step_noalloc(p.ref, FAKE, FAKE, FAKE, FAKE, FAKE, 0.0, FAKE, None, None, None, None) \
+        if _no_device() else B.LSA_ERR_HIP
+    assert rc == B.LSA_ERR_HIP, B.last_error()  # past the size check; there is no device here
+
+
 def test_kv_pack_rejects_bad_arguments_without_launching():
     """lsa_kv_pack validates on the host: first tokens outside [0, ctx], strides
     that are not non-negative multiples of 8 elements, missing or misaligned
