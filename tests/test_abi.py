@@ -403,3 +403,28 @@ def test_hip_failure_is_reported_as_lsa_err_hip():
     with pytest.raises(L.LsaError) as e:
         L.lsa_score_chunks(p, FAKE, FAKE, FAKE, stream=0)
     assert e.value.status == B.LSA_ERR_HIP
+
+
+def _attention_units(ctx, keep, hq, hkv, chunk=64):
+    """Workgroups of the attention's split grid, from the partials in the workspace."""
+    p = L.Problem([chunk * n for n in ctx], chunk, keep, hq, hkv)
+    rows_pad = (hq // hkv + 15) // 16 * 16
+    align = lambda x: (x + 255) // 256 * 256
+    rest = align(sum(ctx) * 4) + align(len(ctx) * max(keep) * 4) + 2 * align(len(ctx) * 4) + align(len(ctx) * hkv * 4)
+    return (L.lsa_workspace_size(p) - rest + 512) // (rows_pad * (128 + 2) * 4)
+
+
+def test_equal_splits_rule():
+    """Batches of more than 8 sequences with at least 24 tiles for each of 1,024
+    workgroups take equal splits, at most 1,024 workgroups in all; others take
+    splits in proportion for one resident round."""
+    ragged = [400 + 331 * i % 1900 for i in range(9)]
+    keep = lambda t: [max(1, n * t // sum(ragged)) for n in ragged]  # t kept chunks in all
+    above, below = keep(1024 * 24 // 2 // 16 + 12), keep(1024 * 24 // 2 // 16 - 3)
+    assert 900 < _attention_units(ragged, above, 32, 16) <= 1024
+    assert 460 < _attention_units(ragged, below, 32, 16) < 600  # too few tiles: one round in proportion
+    assert 220 < _attention_units(ragged[:8], above[:8], 32, 16) < 300  # eight sequences: one workgroup per CU
+    assert _attention_units([4000] * 16, [400] * 16, 32, 8) == 1024
+    # 256 splits per sequence at most, also where equal ones would be more
+    one = [60000] + [64] * 8
+    assert _attention_units(one, [20000] + [6] * 8, 4, 1) == 256 + 8
