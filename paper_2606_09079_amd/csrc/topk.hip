@@ -318,7 +318,7 @@ __device__ __forceinline__ float key_score(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
 
-// The k largest nonzero keys of kk (key q * 1024 + tid in slot q), 1 <= k <=
+// The k largest nonzero keys of kk (key q * 1024 + tid < n in slot q), 1 <= k <=
 // the number of nonzero keys, where the scores spread: one histogram of BINS
 // bins of equal width between the smallest and the largest score leaves a
 // handful of keys in the threshold bin, which one ranking settles, in place of
@@ -326,10 +326,19 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // in that bin).  Mapping a score to its bin is non-decreasing, so the bins keep
 // the order.  Afterwards bm_gt marks the keys above the k-th largest, bm_eq
 // those equal to it, and *krem is how many of the latter are kept.  Returns
-// false, with nothing marked, when the threshold bin holds more than 64 keys
-// (many equal scores, or an outlier that squeezes the others together).
+// false, with nothing marked, when the threshold bin holds more than kRanked
+// keys (many equal scores, or an outlier that squeezes the others together).
+// Where a wave sees that coming, a bin with more than kCrowd + 8192 / n of its
+// first 64 keys (half of what kRanked of n keys would put there), it counts none
+// of its keys: the atomics of a crowded bin take turns.  The fused step at
+// 16,384 keys, radix passes alone / this: normal scores 19.3 / 18.1 us, an
+// outlier that squeezes them into one bin 19.3 / 20.7 (36.8 without the check),
+// half of them masked 21.9 / 23.5 (38.8).
+constexpr uint32_t kRanked = 256;
+constexpr int kCrowd = 6;
 template <int KPT, int BINS, bool INT>
-__device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], uint32_t k, const SelLds& S, uint32_t* krem) {
+__device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], int n, uint32_t k, const SelLds& S,
+                                              uint32_t* krem) {
   constexpr int kPer = BINS / kSelThreads;  // bins per thread
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t* ends = S.cand + 64;  // per wave: the largest key, the largest complement of a key
@@ -348,18 +357,30 @@ __device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], uint32_
 #pragma unroll
   for (int j = 0; j < kPer; ++j) S.hist[j * kSelThreads + tid] = 0u;
   if (tid < kSelMaxN / 128) reinterpret_cast<uint4*>(S.bm_eq)[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) S.sh[2] = 0u;  // 1: crowded
   __syncthreads();
   hi = wave_max_u32(lane < kSelWaves ? ends[lane] : 0u);
   lo = ~wave_max_u32(lane < kSelWaves ? ends[kSelWaves + lane] : 0u);
   const float least = key_score<INT>(lo), span = key_score<INT>(hi) - least;
   const float scale = span > 0.f ? (float)(BINS - 1) / span : 0.f;
   int bin[KPT];
+  bin[0] = min((int)((key_score<INT>(kk[0]) - least) * scale), BINS - 1);
+  const uint64_t live = __ballot(kk[0] != 0u);
+  const int first = __builtin_amdgcn_readlane(bin[0], live != 0ull ? __builtin_ctzll(live) : 0);
+  if (((int)__popcll(__ballot(bin[0] == first) & live) - kCrowd) * n > 8192) {  // wave-uniform
+    if (lane == 0) S.sh[2] = 1u;
+  } else {
 #pragma unroll
-  for (int q = 0; q < KPT; ++q) {
-    bin[q] = min((int)((key_score<INT>(kk[q]) - least) * scale), BINS - 1);
-    if (kk[q] != 0u) atomicAdd(&S.hist[bin[q]], 1u);
+    for (int q = 0; q < KPT; ++q) {
+      if (q > 0) bin[q] = min((int)((key_score<INT>(kk[q]) - least) * scale), BINS - 1);
+      if (kk[q] != 0u) atomicAdd(&S.hist[bin[q]], 1u);
+    }
   }
   __syncthreads();
+  if (S.sh[2] != 0u) {  // uniform
+    __syncthreads();
+    return false;
+  }
   {
     uint32_t c[kPer], mine = 0u;  // bins kPer t .. of thread t
 #pragma unroll
@@ -379,36 +400,58 @@ __device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], uint32_
       if (cum < k && cum + c[j] >= k) {
         S.sh[0] = (uint32_t)(kPer * tid + j);
         S.sh[1] = k - cum;
+        S.sh[2] = c[j] > kRanked ? 1u : 0u;
       }
       cum += c[j];
     }
   }
   __syncthreads();
+  if (S.sh[2] != 0u) {  // uniform
+    __syncthreads();
+    return false;
+  }
   const int B0 = (int)S.sh[0];
   const uint32_t kr = S.sh[1];
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     if (kk[q] != 0u && bin[q] == B0) {
-      const uint32_t at = atomicAdd(&S.sh[3], 1u);
-      if (at < 64u) S.cand[at] = kk[q];
+      S.cand[atomicAdd(&S.sh[3], 1u)] = kk[q];
     }
   }
   __syncthreads();
-  const int m = (int)S.sh[3];
-  if (m > 64) {  // uniform
+  const int m = (int)S.sh[3];  // at most kRanked
+  uint32_t T;
+  if (m <= 64) {  // uniform: every wave ranks them, one per lane
+    const uint32_t mine = lane < m ? S.cand[lane] : 0u;
+    uint32_t above = 0u, same = 0u;
+    for (int i = 0; i < m; ++i) {
+      const uint32_t v = lane_bcast(mine, i);
+      above += v > mine ? 1u : 0u;
+      same += v == mine ? 1u : 0u;
+    }
+    const int at = __builtin_ctzll(__ballot(lane < m && above < kr && above + same >= kr));
+    T = lane_bcast(mine, at);
+    *krem = kr - lane_bcast(above, at);
+  } else {  // 4 threads per key
+    constexpr int kShare = kSelThreads / (int)kRanked;
+    const int i = tid / kShare;
+    const uint32_t mine = i < m ? S.cand[i] : 0u;
+    uint32_t rank = 0u;  // keys above in the low half, keys equal in the high half
+    for (int j = tid % kShare; j < m; j += kShare) {
+      const uint32_t v = S.cand[j];
+      rank += (v > mine ? 1u : 0u) + (v == mine ? 0x10000u : 0u);
+    }
+#pragma unroll
+    for (int off = 1; off < kShare; off *= 2) rank += __shfl_xor(rank, off);
+    const uint32_t above = rank & 0xFFFFu;
+    if (i < m && above < kr && above + (rank >> 16) >= kr) {  // (equal keys write the same)
+      S.sh[0] = mine;
+      S.sh[1] = kr - above;
+    }
     __syncthreads();
-    return false;
+    T = S.sh[0];
+    *krem = S.sh[1];
   }
-  const uint32_t mine = lane < m ? S.cand[lane] : 0u;
-  uint32_t above = 0u, same = 0u;
-  for (int i = 0; i < m; ++i) {
-    const uint32_t v = lane_bcast(mine, i);
-    above += v > mine ? 1u : 0u;
-    same += v == mine ? 1u : 0u;
-  }
-  const int at = __builtin_ctzll(__ballot(lane < m && above < kr && above + same >= kr));
-  const uint32_t T = lane_bcast(mine, at);
-  *krem = kr - lane_bcast(above, at);
   uint64_t* gdst = reinterpret_cast<uint64_t*>(S.bm_gt) + wave;
   uint64_t* edst = reinterpret_cast<uint64_t*>(S.bm_eq) + wave;
 #pragma unroll
@@ -485,6 +528,16 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
     for (int q = 0; q < KPT; ++q)
       mp[q] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(msrc, tid * 4, q * kSelThreads * 4, 0);
   }
+  // Whether the spread selection is tried (below); where it is not, the radix
+  // passes' histogram is cleared while the keys load.
+  constexpr bool kSpread = MODE != kKeysFromI32 && !((RECALL || MODE == kKeysFromF32) && KPT == kSelKPT);
+  auto clear = [&] {
+#pragma unroll
+    for (int q = 0; q < kSelSub; ++q)
+      reinterpret_cast<uint4*>(hist)[q * kSelThreads + tid] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < kSelMaxN / 128) reinterpret_cast<uint4*>(bm_eq)[tid] = make_uint4(0u, 0u, 0u, 0u);
+  };
+  if constexpr (!kSpread) clear();
   if constexpr (RECALL) {
     // keys of the first layer, then the largest over the other indexer layers
 #pragma unroll
@@ -500,7 +553,7 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
   }
   // Keys to order; the recall keeps the keys at or above the key of +0.0 (the
   // others become 0), at most K_max = keep[b] of them.
-  if constexpr (MODE != kKeysReady && MODE != kKeysReadyInt && !RECALL) {
+  if constexpr (kSpread && MODE != kKeysReady && MODE != kKeysReadyInt && !RECALL) {
 #pragma unroll
     for (int q = 0; q < KPT; ++q) kk[q] = q * kSelThreads + tid < n ? order_key<MODE>(kk[q]) : 0u;
   }
@@ -528,18 +581,15 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
   // 1,638 mapped keys 6.9 -> 5.8, 2,048 integer keys 6.0 -> 5.7.  Not for raw
   // integers, whose least key is 0, nor for the recall of over 8,192 entries,
   // most of whose keys are dropped before the radix passes count them: 8.1 us
-  // against 8.3.)
+  // against 8.3, nor for raw scores of over 8,192 entries: 8.2 against 8.3.)
   uint32_t krem = 0u;
   bool found = false;
-  if constexpr (MODE != kKeysFromI32 && !(RECALL && KPT == kSelKPT))
+  if constexpr (kSpread)
     found = select_spread<KPT, (KPT >= 8 ? 4096 : 1024), MODE == kKeysReadyInt>(
-        kk, (uint32_t)k, SelLds{hist, cand, keys, tot, bm_gt, bm_eq, sh}, &krem);
+        kk, n, (uint32_t)k, SelLds{hist, cand, keys, tot, bm_gt, bm_eq, sh}, &krem);
   if (!found) {  // uniform
-#pragma unroll
-    for (int q = 0; q < kSelSub; ++q)
-      reinterpret_cast<uint4*>(hist)[q * kSelThreads + tid] = make_uint4(0u, 0u, 0u, 0u);
-    if (tid < kSelMaxN / 128) reinterpret_cast<uint4*>(bm_eq)[tid] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
+    if constexpr (kSpread) clear();
+    if constexpr (kSpread || !RECALL) __syncthreads();
 
     // First digit (top 12 bits).  The atomic returns the key's rank among the
     // keys of its bin and quarter, which later places it in the candidate list.
@@ -548,6 +598,7 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
     bool in[KPT];
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
+      if constexpr (!kSpread && !RECALL) kk[q] = q * kSelThreads + tid < n ? order_key<MODE>(kk[q]) : 0u;
       in[q] = RECALL ? kk[q] != 0u : q * kSelThreads + tid < n;
       bin[q] = kk[q] >> 20;
       rk[q] = in[q] ? atomicAdd(&hist[bin[q] * kSelSub + sub], 1u) : 0u;
@@ -1155,7 +1206,7 @@ two_level_select_kernel(SeqTable t, TwoLevelSelArgs a) {
     }
     if (k1 < recalled) {
       uint32_t krem1;
-      if (!select_spread<kPer, 1024, false>(c1, k1, S, &krem1)) krem1 = select_pass(c1, k1, S);
+      if (!select_spread<kPer, 1024, false>(c1, (int)recalled, k1, S, &krem1)) krem1 = select_pass(c1, k1, S);
       uint32_t unused;
       const uint32_t rw = kept_word(S, (int)recalled, krem1, &unused);
       if (tid < kCompactMax / 32) rec[tid] = rw;
@@ -1168,7 +1219,7 @@ two_level_select_kernel(SeqTable t, TwoLevelSelArgs a) {
     }
     k2 = min((uint32_t)max(a.keep2[b], 1), k1);
     uint32_t krem2;
-    if (!select_spread<kPer, 1024, false>(c2, k2, S, &krem2)) krem2 = select_pass(c2, k2, S);
+    if (!select_spread<kPer, 1024, false>(c2, (int)recalled, k2, S, &krem2)) krem2 = select_pass(c2, k2, S);
     uint32_t pos;
     uint32_t kept = kept_word(S, (int)recalled, krem2, &pos);
     while (kept != 0u) {

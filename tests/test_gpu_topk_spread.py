@@ -1,7 +1,7 @@
 """Top-k up to 16,384 chunks where one histogram over the scores' range settles
 the selection and where it must hand over to the radix passes: outliers that
-squeeze the other scores into one bin, many equal scores at the boundary, two
-clusters, subnormal and huge ranges, all-equal scores, at the edges of the
+squeeze the other scores into one bin or a few, masked scores, many equal scores
+at the boundary (a threshold bin of 65 to 256 keys), two clusters, subnormal and huge ranges, all-equal scores, at the edges of the
 kernel's variants.  Kept sets equal a stable sort of the same scores.
 """
 from __future__ import annotations
@@ -19,6 +19,10 @@ def _scores(rng, n, kind):
     if kind == "outlier":
         x[0, n // 2] = np.float32(1e30)
         x[1, n // 3] = np.float32(-1e30)
+    elif kind == "squeezed":  # one that leaves the others 20 bins each standard deviation
+        x[:, n // 2] = np.float32(200.0)
+    elif kind == "masked":  # half at the type's lowest value
+        x[:, n // 2:] = np.finfo(np.float32).min
     elif kind == "boundary":  # 70 equal scores where the set ends
         x = np.sort(x, axis=1)[:, ::-1].copy()
         at = max(0, n // 10 - 35)
@@ -36,7 +40,8 @@ def _scores(rng, n, kind):
     return x
 
 
-@pytest.mark.parametrize("kind", ["normal", "outlier", "boundary", "clusters", "subnormal", "huge", "equal"])
+@pytest.mark.parametrize("kind", ["normal", "outlier", "squeezed", "masked", "boundary", "clusters", "subnormal", "huge",
+                                  "equal"])
 @pytest.mark.parametrize("n", [1, 2, 64, 65, 1023, 2048, 2049, 4097, 8192, 8193, 16384])
 def test_topk_spread(n, kind):
     rng = np.random.default_rng(n + len(kind))
@@ -53,7 +58,7 @@ def test_recall_spread(n):
     import torch
     import paper_2606_09079_amd as L
     rng = np.random.default_rng(n)
-    for kind in ("normal", "outlier", "huge", "equal"):
+    for kind in ("normal", "outlier", "squeezed", "masked", "huge", "equal"):
         x = _scores(rng, n, kind)
         r = x.max(0)
         for k in (1, max(1, n // 8), n):
