@@ -129,7 +129,7 @@ lsa_status plan_splits(const lsa_problem* p, Plan* pl, const lsa_two_level* tl, 
   }
   const int srows = score_rows_per_wg(p->emb_dtype, p->emb_dim, p->n_lookahead, all_chunks);
   const int tpc = C / 32;
-  P.one_split = rows <= 16 && sel_most * tpc <= kOneSplitTiles;
+  P.one_split = rows <= 16 && sel_most * tpc <= one_split_tiles((int64_t)B * p->n_kv_heads);
   const int target = rows <= 16 && B <= kFewSequences ? kTargetWorkgroupsFew : kTargetWorkgroups;
   // Batches: the fewest tiles per split with which the grid stays within two
   // resident rounds (0: splits in proportion, one round).  Splits in proportion

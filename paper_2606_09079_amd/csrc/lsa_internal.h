@@ -87,12 +87,15 @@ constexpr int kFewSplits = 16;   // splits per (sequence, kv head) up to which t
 // 2% of 1,024.
 constexpr int kBatchWorkgroups = 1024;
 constexpr int kBatchTiles = 24;
-// At most this many 32-token tiles per (sequence, KV head) and 16 rows: one
-// workgroup of kOneSplitWaves waves takes them all and writes the output itself.
-// One compute unit streams about 90 KB/us, so 16 tiles (256 KiB) take 7.0 us
-// against 7.9 with the split kernel's own merge and 8.5 with a combine launch;
-// 32 tiles take 9.4 against 8.4.
-constexpr int kOneSplitTiles = 16;
+// Up to this many 32-token tiles per (sequence, KV head), with at most 16 rows,
+// one workgroup of kOneSplitWaves waves takes them all and writes the output
+// itself.  One compute unit streams few tiles quickly enough, and the more
+// (sequence, KV head) pairs there are, the less the other units are missed.
+// Fused step with K/V from HBM, several splits / one, us: 8 pairs 10 tiles 9.9 /
+// 9.5, 12 10.3 / 10.3, 14 10.6 / 11.2, 16 11.0 / 11.7; one or two pairs 10 tiles
+// 9.2 / 9.3, 12 9.4 / 10.0; 64 pairs 16 tiles 13.2 / 13.2, 20 14.4 / 14.8; 128
+// pairs 16 tiles 16.8 / 14.4, 24 19.4 / 17.8; 256 pairs 24 tiles 28 / 24.
+inline int one_split_tiles(int64_t pairs) { return pairs >= 128 ? 24 : pairs >= 64 ? 16 : pairs >= 4 ? 12 : 10; }
 constexpr int kOneSplitWaves = 8;
 constexpr int kMaxSplits = 256;  // splits per (sequence, kv head, row group)
 

@@ -1,5 +1,5 @@
-"""Attention over short kept lists (at most 16 tiles of 32 tokens per sequence),
-which one workgroup per (sequence, KV head) takes whole and writes itself: from
+"""Attention over short kept lists (at most 10 to 24 tiles of 32 tokens per
+sequence, by the number of sequences and KV heads), which one workgroup per (sequence, KV head) takes whole and writes itself: from
 no kept chunk to just past the limit, one to 16 query rows, ragged batches and
 a partial last chunk, token by token against the oracle.
 """
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("chunk,counts", [(64, [8, 1, 5]), (64, [0, 8]), (64, [9, 2]), (128, [4, 3, 1]), (128, [5]),
-                                          (64, [2] * 12)])
+                                          (64, [2] * 12), (64, [5]), (64, [6]), (64, [6] * 3), (64, [7] * 3),
+                                          (64, [8] * 16), (64, [9] * 16)])
 @pytest.mark.parametrize("hq,hkv,tq", [(8, 8, 1), (12, 4, 5), (8, 1, 2)])
 def test_one_split(chunk, counts, hq, hkv, tq):
     import torch
