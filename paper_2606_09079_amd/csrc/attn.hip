@@ -12,7 +12,7 @@
 // fp32; the softmax weights P enter the PV product as bf16 hi + lo parts (two
 // MFMAs per product), which keeps ~16 significant bits.
 //
-// attn_split_kernel (rows <= 32) on v_mfma_f32_16x16x32_bf16.  The 4 waves of
+// attn_split_kernel (rows <= 16, and <= 32 with long kept lists) on v_mfma_f32_16x16x32_bf16.  The 4 waves of
 //   a workgroup take every fourth tile of the split (wave w: tiles w, w + 4,
 //   ...), each streaming its own tiles straight into registers (1 KiB per load
 //   instruction, nontemporal hint, two tiles in flight per wave), and merge
@@ -27,7 +27,7 @@
 //     8*(lane/16)..+7 of query row lane%16 -- the A-operand layout PV needs.
 //   * PV computes O = P V with the tile's 32 tokens as K and 16 head dims per
 //     MFMA as N.
-// attn_rows_kernel (33..128 rows) on v_mfma_f32_32x32x16_bf16.  Every wave
+// attn_rows_kernel (33..128 rows, 17..32 with short kept lists) on v_mfma_f32_32x32x16_bf16.  Every wave
 //   owns 32 rows and needs every tile, so each tile is copied once per
 //   workgroup from HBM into LDS (global->LDS copies into MFMA operand order,
 //   three tiles ahead, five 16 KiB buffers).  QK computes S^T = K Q^T and PV
@@ -525,7 +525,7 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
 }
 
 
-// More than 32 query rows per KV head (rows = G * n_qtok, up to 128).  One
+// More than 16 query rows per KV head (rows = G * n_qtok, up to 128).  One
 // workgroup per (sequence, kv head, split) serves all the rows, so each K/V
 // tile is fetched from HBM once: every wave copies 4 of the tile's 16 one-KiB
 // pieces (K pieces 0-7, V pieces 8-15) straight into LDS with
@@ -948,10 +948,10 @@ hipError_t launch_c(const SeqTable& t, const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((attn_split_kernel<C, kDirect, 1, kOneSplitWaves>), grid, dim3(64 * kOneSplitWaves), 0, s, t, a);
     return hipGetLastError();
   }
-  if (a.rows > kAttnSplitRows)
-    hipLaunchKernelGGL((attn_rows_kernel<C>), grid, dim3(kThreads), 0, s, t, a);
-  else if (a.rows > 16)
+  if (a.two_blocks)
     hipLaunchKernelGGL((attn_split_kernel<C, kParts, 2, kAttnWaves>), grid, dim3(kThreads), 0, s, t, a);
+  else if (a.rows > 16)
+    hipLaunchKernelGGL((attn_rows_kernel<C>), grid, dim3(kThreads), 0, s, t, a);
   else if (a.arrive != nullptr)
     hipLaunchKernelGGL((attn_split_kernel<C, kMerge, 1, kAttnWaves>), grid, dim3(kThreads), 0, s, t, a);
   else

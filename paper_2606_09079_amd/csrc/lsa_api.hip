@@ -43,6 +43,7 @@ struct Plan {
   int64_t chunk_stride = 0, head_stride = 0;
   int64_t n_units = 0;
   bool equal_splits = false;
+  bool two_blocks = false;  // 17 to 32 rows in the split kernel
   bool one_split = false;  // every (b, g) in one workgroup that writes the output
   size_t emb_elem = 0;
   // two-level path: history chunks (before the window) per sequence, and the
@@ -120,16 +121,20 @@ lsa_status plan_splits(const lsa_problem* p, Plan* pl, const lsa_two_level* tl, 
     return std::min<int64_t>({(int64_t)tl->core_keep[b], (int64_t)p->keep[b], w0}) + (n - w0);
   };
   // First pass: the total kept-chunk bound, which sizes the splits.
-  int64_t sel_total = 0, sel_most = 0, all_chunks = 0;
+  int64_t sel_total = 0, sel_most = 0, all_chunks = 0, sel_usual = 0;
   for (int b = 0; b < B; ++b) {
     const int64_t L = std::max<int64_t>(p->ctx_tokens[b], 0);
     all_chunks += L / C + (L % C != 0);
     sel_total += kept_bound(b);
+    // (lookahead queries of one sequence mostly agree: the union is about twice one set)
+    sel_usual += std::min(kept_bound(b), (int64_t)2 * std::max(p->keep[b], 0));
     sel_most = std::max(sel_most, kept_bound(b));
   }
   const int srows = score_rows_per_wg(p->emb_dtype, p->emb_dim, p->n_lookahead, all_chunks);
   const int tpc = C / 32;
   P.one_split = rows <= 16 && sel_most * tpc <= one_split_tiles((int64_t)B * p->n_kv_heads);
+  P.two_blocks = rows > 16 && rows <= kAttnSplitRows &&
+                 sel_usual * tpc * p->n_kv_heads >= (int64_t)kTwoBlockTiles * kTargetWorkgroups;
   const int target = rows <= 16 && B <= kFewSequences ? kTargetWorkgroupsFew : kTargetWorkgroups;
   // Batches: the fewest tiles per split with which the grid stays within two
   // resident rounds (0: splits in proportion, one round).  Splits in proportion
@@ -355,6 +360,7 @@ lsa_status run_attn(const lsa_problem* p, const Plan& P, const uint16_t* q, cons
   a.rows = P.rows;
   a.rows_pad = P.rows_pad;
   a.one_split = P.one_split ? 1 : 0;
+  a.two_blocks = P.two_blocks ? 1 : 0;
   a.few_splits = max_splits(P) <= kFewSplits ? 1 : 0;
   a.arrive = P.t.arrive;  // set (and zeroed by the scoring kernel) only where merge_in_split(P)
   LSA_HIP(launch_attn(P.t, a, p->chunk_size, s), "attention launch");

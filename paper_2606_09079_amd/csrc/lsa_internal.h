@@ -54,6 +54,7 @@ struct AttnArgs {
   uint32_t* arrive;      // NULL: a combine kernel merges the splits.  Else one counter per (b, g), zero on
                          // entry: the last split workgroup of (b, g) to finish merges them (split kernel only)
   int32_t one_split;     // 1: one split per (b, g), whose workgroup writes the output
+  int32_t two_blocks;    // 1: 17 to 32 rows in the split kernel
   int32_t few_splits;    // 1: every sequence has at most 16 splits (the merge order of the few-split combine)
 };
 
@@ -61,13 +62,18 @@ struct AttnArgs {
 constexpr int kAttnWaves = 4;          // waves per workgroup
 constexpr int kAttnRowsPerWave = 16;   // MFMA tile rows
 constexpr int kHeadDim = 128;
-// Query rows per KV head up to which the split kernel serves: 17 to 32 rows as
-// two 16-row blocks against the same K/V registers.  32 rows, 110,500 kept
-// tokens: 83 us against 90 with the many-rows kernel (whose four waves would
-// leave three without a row block); 24 rows, 16 sequences: 238 against 260.
-// With four blocks (33 to 64 rows) the registers do not suffice: 295 us
+// 17 to kAttnSplitRows query rows per KV head: the split kernel takes them as two
+// 16-row blocks against the same K/V registers where the kept lists hold at least
+// kTwoBlockTiles tiles for each of its workgroups, and the many-rows kernel (whose
+// four waves leave three without a row block, but which prefetches three tiles)
+// below: the two-block kernel needs every register, spills six and starts slowly.
+// 1 to 16 sequences, K/V from HBM, many-rows / two blocks, us: 4 kept chunks 24
+// rows 7.3 / 10.6; 16 tiles per workgroup 34.6 / 36.3 (24 rows), 35.0 / 37.4 (32);
+// 32 57.6 / 57.3, 58.4 / 59.0; 48 80.8 / 77.7, 81.5 / 80.2; 96 151 / 141, 150 /
+// 142.  With four blocks (33 to 64 rows) the registers do not suffice: 295 us
 // against 108.
 constexpr int kAttnSplitRows = 32;
+constexpr int kTwoBlockTiles = 48;
 // Split-K sizing: the attention grid is sized to one resident round of the
 // MI355X (256 CUs x 2 workgroups of 256 threads at <= 256 registers).  With
 // at most kFewSequences sequences the split kernel (<= 16 rows) runs one
