@@ -66,7 +66,7 @@ constexpr int kHeadDim = 128;
 // 16-row blocks against the same K/V registers where the kept lists hold at least
 // kTwoBlockTiles tiles for each of its workgroups, and the many-rows kernel (whose
 // four waves leave three without a row block, but which prefetches three tiles)
-// below: the two-block kernel needs every register, spills six and starts slowly.
+// below: the two-block kernel needs every register, spills four and starts slowly.
 // 1 to 16 sequences, K/V from HBM, many-rows / two blocks, us: 4 kept chunks 24
 // rows 7.3 / 10.6; 16 tiles per workgroup 34.6 / 36.3 (24 rows), 35.0 / 37.4 (32);
 // 32 57.6 / 57.3, 58.4 / 59.0; 48 80.8 / 77.7, 81.5 / 80.2; 96 151 / 141, 150 /

@@ -272,13 +272,29 @@ score_select_kernel(SeqTable t, const uint8_t* __restrict__ qe, const uint8_t* _
 // exactly once.  A lane's four scores of a group are four consecutive chunks of
 // one query and leave as one 16-byte store.
 constexpr int kMfmaMinQueries = 4;
-// 16-chunk groups per wave: the groups share the wave's query operand, so with
-// two the query embeddings are read from L2 half as often, which pays only
-// where the grid stays large.  65,536 chunks, 16 queries: 9.1 us with two, 10.1
-// with one, 9.7 with four; 13,300 chunks, 4 queries: 4.9, 4.8 and 7.0; 27,000
-// chunks, 8 queries: 7.2, 6.3 and 7.8.
-constexpr int64_t kMfmaTwoGroups = 32768;  // chunks in the call from which waves take two groups
-int mfma_groups(int64_t total_chunks) { return total_chunks >= kMfmaTwoGroups ? 2 : 1; }
+// 16-chunk groups per wave, 1, 2 or (up to D = 256, whose operands fit the
+// registers) 4.  The groups share the wave's query operand, and a compute unit
+// holds one workgroup at a time, so a call takes ceil(chunks / (64 groups * 256))
+// rounds of a length of about groups + queries / 24 (four groups a little more):
+// the fewest such units.  D = 256, embeddings from HBM, one / two / four groups,
+// us: 16,000 chunks 4 queries 4.2 / 4.9 / 6.6; 24,000 16 queries 6.6 / 5.6 / 7.4;
+// 33,000 16 queries 8.3 / 8.9 / 7.5, 4 queries 6.6 / 7.3 / 6.7; 66,000 8 queries
+// 10.2 / 10.6 / 12.8; 98,000 16 queries 14.4 / 13.4 / 14.9; 262,144 32.5 / 31.8 /
+// 30.5.
+constexpr int64_t kMfmaRound = 256;  // workgroups
+int mfma_groups(int32_t emb_dim, int32_t n_lookahead, int64_t total_chunks) {
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int g = 1; g <= (emb_dim <= 256 ? 4 : 2); g *= 2) {
+    const int64_t rounds = (total_chunks + 64 * g * kMfmaRound - 1) / (64 * g * kMfmaRound);
+    const int64_t cost = rounds * (n_lookahead + 24 * g + (g == 4 ? 5 : 0));
+    if (cost < least) {
+      least = cost;
+      best = g;
+    }
+  }
+  return best;
+}
 constexpr int mfma_rows_per_wg(int groups) { return 4 * 16 * groups; }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -356,7 +372,10 @@ hipError_t launch_mfma_g(const SeqTable& t, const void* qe, const void* E, void*
 template <int D>
 hipError_t launch_mfma_d(const SeqTable& t, const void* qe, const void* E, void* scores, bool keys, hipStream_t s) {
   // (t was laid out with the same rule, score_rows_per_wg)
-  if (mfma_groups(t.chunk_off[t.batch]) == 2) return launch_mfma_g<D, 2>(t, qe, E, scores, keys, s);
+  const int groups = mfma_groups(D, t.n_lookahead, t.chunk_off[t.batch]);
+  if constexpr (D <= 256)
+    if (groups == 4) return launch_mfma_g<D, 4>(t, qe, E, scores, keys, s);
+  if (groups == 2) return launch_mfma_g<D, 2>(t, qe, E, scores, keys, s);
   return launch_mfma_g<D, 1>(t, qe, E, scores, keys, s);
 }
 
@@ -419,7 +438,7 @@ int rows_dt(int32_t D) {
 }  // namespace
 
 int score_rows_per_wg(int32_t emb_dtype, int32_t emb_dim, int32_t n_lookahead, int64_t total_chunks) {
-  if (use_mfma(emb_dtype, n_lookahead)) return mfma_rows_per_wg(mfma_groups(total_chunks));
+  if (use_mfma(emb_dtype, n_lookahead)) return mfma_rows_per_wg(mfma_groups(emb_dim, n_lookahead, total_chunks));
   switch (emb_dtype) {
     case LSA_F32: return rows_dt<LSA_F32>(emb_dim);
     case LSA_BF16: return rows_dt<LSA_BF16>(emb_dim);
