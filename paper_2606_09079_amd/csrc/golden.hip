@@ -550,9 +550,11 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
       mine_sum += mine[j];
     }
     uint64_t incl = mine_sum;
+    int from = lane;  // (opaque, as in wave_reduce)
+    asm volatile("" : "+v"(from));
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      const uint64_t y = __shfl_up(incl, off);
+      const uint64_t y = __shfl(incl, from - off);
       if (lane >= off) incl += y;
     }
     if (lane == 63) red[0][wave] = incl;
@@ -638,12 +640,14 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
 
   // ---- members: candidates above T, and the r entries equal to T with the lowest ids
   const bool some = r != ties;
+  int t0 = tid;  // (opaque, as in wave_reduce)
+  asm volatile("" : "+v"(t0));
   for (int w0 = 0; w0 < words; w0 += kLdsWords) {
     const int nw = min(words - w0, kLdsWords);
     __syncthreads();
-    for (int w = tid; w < nw; w += kRowThreads) lbm[w] = 0u;
+    for (int w = t0; w < nw; w += kRowThreads) lbm[w] = 0u;
     __syncthreads();
-    for (int i = tid; i < nl; i += kRowThreads) {
+    for (int i = t0; i < nl; i += kRowThreads) {
       const uint32_t k = lkey[i], e = lidx[i];
       bool in = k >= T;
       if (some && k == T) {
@@ -661,11 +665,11 @@ golden_row_kernel(GoldenTable gt, GoldenArgs a) {
       if (tid == 0) bm[kOpenWord] = kOpenRow;
       return;
     }
-    for (int w = tid; w < nw; w += kRowThreads) bm[w0 + w] = lbm[w];
+    for (int w = t0; w < nw; w += kRowThreads) bm[w0 + w] = lbm[w];
   }
   if (a.nucleus_size != nullptr) {
     uint32_t n_in = 0u;
-    for (int i = tid; i < nl; i += kRowThreads) n_in += lkey[i] > T ? 1u : 0u;
+    for (int i = t0; i < nl; i += kRowThreads) n_in += lkey[i] > T ? 1u : 0u;
     n_in = wave_reduce(n_in, [](uint32_t p, uint32_t s) { return p + s; });
     if (lane == 0) red[1][wave] = n_in;
     __syncthreads();
