@@ -377,16 +377,17 @@ __device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], int n, 
     }
   }
   __syncthreads();
-  if (S.sh[2] != 0u) {  // uniform
-    __syncthreads();
-    return false;
-  }
   {
+    const uint32_t crowded = S.sh[2];
     uint32_t c[kPer], mine = 0u;  // bins kPer t .. of thread t
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       c[j] = S.hist[kPer * tid + j];
       mine += c[j];
+    }
+    if (crowded != 0u) {  // uniform
+      __syncthreads();
+      return false;
     }
     const uint32_t incl = wave_scan_incl(mine);
     if (lane == 63) S.tot[wave] = incl;
@@ -406,12 +407,12 @@ __device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], int n, 
     }
   }
   __syncthreads();
+  const int B0 = (int)S.sh[0];
+  const uint32_t kr = S.sh[1];
   if (S.sh[2] != 0u) {  // uniform
     __syncthreads();
     return false;
   }
-  const int B0 = (int)S.sh[0];
-  const uint32_t kr = S.sh[1];
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     if (kk[q] != 0u && bin[q] == B0) {
@@ -479,7 +480,7 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
   __shared__ __align__(16) uint32_t tot[kSelWaves];
   __shared__ __align__(16) uint32_t bm_gt[kSelMaxN / 32];  // chunks above T, bit i % 32 of word i / 32
   __shared__ __align__(16) uint32_t bm_eq[kSelMaxN / 32];  // chunks equal to T
-  __shared__ uint32_t sh[4];
+  __shared__ __align__(16) uint32_t sh[4];
   __shared__ uint32_t nonneg[kSelWaves];  // recall: keys >= the key of +0.0, per wave
 
   // (sequence, query) of this workgroup; the numbers of sequence 0 are loaded
@@ -1121,7 +1122,7 @@ two_level_select_kernel(SeqTable t, TwoLevelSelArgs a) {
   __shared__ __align__(16) uint32_t bm_gt[kSelMaxN / 32];
   __shared__ __align__(16) uint32_t bm_eq[kSelMaxN / 32];
   __shared__ uint32_t rec[kSelMaxN / 32];
-  __shared__ uint32_t sh[4];
+  __shared__ __align__(16) uint32_t sh[4];
   __shared__ __align__(16) uint32_t group_at[kSelMaxN / 64];
   constexpr int kCompactMax = 4096;  // recalled entries up to which they are closed up
   static_assert(3 * kCompactMax <= kSelMaxN, "the closed-up entries share the keys' space");
