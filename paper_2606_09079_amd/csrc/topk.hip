@@ -318,8 +318,8 @@ __device__ __forceinline__ float key_score(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
 
-// The k largest nonzero keys of kk (key q * 1024 + tid < n in slot q), 1 <= k <=
-// the number of nonzero keys, where the scores spread: one histogram of BINS
+// The k largest nonzero keys of kk (key q * 1024 + tid < n in slot q), k >= 1,
+// where there are that many and the scores spread: one histogram of BINS
 // bins of equal width between the smallest and the largest score leaves a
 // handful of keys in the threshold bin, which one ranking settles, in place of
 // the radix passes' digits (the float keys' first 12 bits put hundreds of keys
@@ -391,7 +391,7 @@ __device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], int n, 
     }
     const uint32_t incl = wave_scan_incl(mine);
     if (lane == 63) S.tot[wave] = incl;
-    if (tid == 0) S.sh[3] = 0u;
+    if (tid == 0) S.sh[1] = S.sh[3] = 0u;
     __syncthreads();
     const uint32_t wt = lane < kSelWaves ? S.tot[lane] : 0u;
     const uint32_t after = lane_bcast(wave_scan_incl(lane > wave ? wt : 0u), 63);
@@ -409,7 +409,9 @@ __device__ __forceinline__ bool select_spread(const uint32_t (&kk)[KPT], int n, 
   __syncthreads();
   const int B0 = (int)S.sh[0];
   const uint32_t kr = S.sh[1];
-  if (S.sh[2] != 0u) {  // uniform
+  // (no bin reaches k where fewer than k keys are nonzero: a NaN with every bit
+  // set maps to key 0, and the radix passes count it by its position)
+  if (S.sh[2] != 0u || kr == 0u) {  // uniform
     __syncthreads();
     return false;
   }

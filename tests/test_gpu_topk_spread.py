@@ -69,3 +69,22 @@ def test_recall_spread(n):
             torch.cuda.synchronize()
             want = _want(r, min(k, int((r >= 0).sum())))
             assert np.array_equal(sel.cpu().numpy()[0, :int(cnt.item())], want), (n, kind, k)
+
+
+@pytest.mark.parametrize("n", [64, 500, 2048, 4097, 8192, 16384])
+@pytest.mark.parametrize("share", [2, 16])
+def test_unset_scores(n, share):
+    """Scores with every bit set (memory that was never written) are NaN and map
+    to key 0: below every other score, in entry order among themselves, whether
+    or not the kept set reaches them."""
+    rng = np.random.default_rng(n * share)
+    x = rng.standard_normal((2, n)).astype(np.float32)
+    order = x.copy()
+    for j in range(2):
+        at = rng.permutation(n)[:n - n // share]
+        x[j].view(np.uint32)[at] = np.uint32(0xFFFFFFFF)
+        order[j, at] = -np.inf
+    for k in sorted({1, n // share, n // share + 1, n - 1, n}):
+        per_query, _ = _topk(x, k, "f32", Q=2)
+        for j in range(2):
+            assert np.array_equal(per_query[j], _want(order[j], k)), (n, share, k, j)
