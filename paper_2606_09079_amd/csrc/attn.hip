@@ -15,7 +15,10 @@
 // attn_split_kernel (rows <= 16, and <= 32 with long kept lists) on v_mfma_f32_16x16x32_bf16.  The 4 waves of
 //   a workgroup take every fourth tile of the split (wave w: tiles w, w + 4,
 //   ...), each streaming its own tiles straight into registers (1 KiB per load
-//   instruction, nontemporal hint, two tiles in flight per wave), and merge
+//   instruction, nontemporal hint; a tile is loaded while the one before it is
+//   computed, and its loads go out once that one has arrived, which the chunk
+//   list's register makes the compiler wait for -- without that wait two whole
+//   tiles were in flight, and the fused steps took the same time), and merge
 //   their (m, l, O) states through LDS.  Interleaved tiles keep the four waves
 //   of a workgroup within a tile of each other where consecutive quarters left
 //   them waiting for the slowest at the merge.
@@ -271,7 +274,7 @@ template <int C, int OUT, int RB, int W>
 __global__ void __launch_bounds__(64 * W, 2)  // 2 waves per SIMD: <= 256 registers
 attn_split_kernel(SeqTable t, AttnArgs a) {
   constexpr bool MERGE = OUT == kMerge;
-  __shared__ float sm_o[W][16 * RB][kOPad];
+  __shared__ __align__(16) float sm_o[W][16 * RB][kOPad];
   __shared__ float sm_m[W][16 * RB], sm_l[W][16 * RB];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -297,19 +300,28 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
   const int T0 = split_first(sd.wg0 + g * ns, s, ns, nTall), T1 = split_first(sd.wg0 + g * ns, s + 1, ns, nTall);
   // wave w takes tiles T0 + w, T0 + w + W, ... of the split
 
-  // ---- query operands: row 16 rb + n16 of block rb
-  bf16x8 qb[RB][4];
+  // ---- query operands: row 16 rb + n16 of block rb.  The second block's wait
+  // in the wave's own part of sm_o, which is free until the merge, and are read
+  // again for every tile: in registers they pushed the tiles' addresses to scratch
+  // (24 and 32 rows, 24 to 96 tiles per workgroup, took 2 to 4% longer).
+  bf16x8 qb[4];
+  typedef bf16x8 __attribute__((may_alias)) bf16x8_in_floats;
+  static_assert(16 * kOPad * sizeof(float) >= 4 * 64 * sizeof(bf16x8) && 16 * kOPad * sizeof(float) % 16 == 0, "sm_o");
+  bf16x8_in_floats* qb1 = reinterpret_cast<bf16x8_in_floats*>(&sm_o[wave][0][0]);  // [4][64]
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = 16 * rb + n16;
+    bf16x8 x[4] = {};
     if (row < rows) {
       const int tq = row / G, h = g * G + row % G;
       const uint16_t* qp = a.q + (((int64_t)b * n_qtok + tq) * n_q_heads + h) * kHeadDim + 8 * kg;
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) qb[rb][jj] = load8(qp + 32 * jj);
-    } else {
+      for (int jj = 0; jj < 4; ++jj) x[jj] = load8(qp + 32 * jj);
+    }
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) qb[rb][jj] = bf16x8{};
+    for (int jj = 0; jj < 4; ++jj) {
+      if (rb == 0) qb[jj] = x[jj];
+      else qb1[64 * jj + lane] = x[jj];
     }
   }
 
@@ -375,10 +387,13 @@ attn_split_kernel(SeqTable t, AttnArgs a) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+      int at = lane;
+      if (rb > 0) asm volatile("" : "+v"(at));  // no copy in registers across tiles
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[jj], qb[rb][jj], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[4 + jj], qb[rb][jj], s1, 0, 0, 0);
+        const bf16x8 qr = rb == 0 ? qb[jj] : qb1[64 * jj + at];
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[jj], qr, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[4 + jj], qr, s1, 0, 0, 0);
       }
       // lane holds logits of query row 16 rb + n16 for tile tokens 8kg + 0..7
       float x[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};

@@ -66,14 +66,14 @@ constexpr int kHeadDim = 128;
 // 16-row blocks against the same K/V registers where the kept lists hold at least
 // kTwoBlockTiles tiles for each of its workgroups, and the many-rows kernel (whose
 // four waves leave three without a row block, but which prefetches three tiles)
-// below: the two-block kernel needs every register, spills four and starts slowly.
-// 1 to 16 sequences, K/V from HBM, many-rows / two blocks, us: 4 kept chunks 24
-// rows 7.3 / 10.6; 16 tiles per workgroup 34.6 / 36.3 (24 rows), 35.0 / 37.4 (32);
-// 32 57.6 / 57.3, 58.4 / 59.0; 48 80.8 / 77.7, 81.5 / 80.2; 96 151 / 141, 150 /
-// 142.  With four blocks (33 to 64 rows) the registers do not suffice: 295 us
-// against 108.
+// below: the two-block kernel starts and merges more slowly.  1 to 16 sequences,
+// K/V from HBM, attention with its combine, many-rows / two blocks, us: 4 tiles per
+// workgroup 16.8 / 19.4 (24 rows), 17.3 / 21.4 (32); 16 33.6 / 34.7, 34.1 / 36.9; 24
+// 45.1 / 44.6, 45.8 / 46.5; 32 57.0 / 54.0, 57.8 / 56.1; 48 77.6 / 73.4, 78.5 / 75.4;
+// 96 146 / 132, 147 / 134.  With four blocks (33 to 64 rows) the registers do not
+// suffice: 295 us against 108.
 constexpr int kAttnSplitRows = 32;
-constexpr int kTwoBlockTiles = 48;
+constexpr int kTwoBlockTiles = 32;
 // Split-K sizing: the attention grid is sized to one resident round of the
 // MI355X (256 CUs x 2 workgroups of 256 threads at <= 256 registers).  With
 // at most kFewSequences sequences the split kernel (<= 16 rows) runs one

@@ -13,7 +13,7 @@ import lsa_synth as synth
 pytestmark = pytest.mark.gpu
 
 HKV = 16
-LIMIT = 48 * 512 // HKV  # tiles per KV head
+LIMIT = 32 * 512 // HKV  # tiles per KV head
 
 
 @pytest.mark.parametrize("chunk", [64, 128])
