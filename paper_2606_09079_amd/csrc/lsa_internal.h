@@ -90,7 +90,12 @@ constexpr int kFewSplits = 16;   // splits per (sequence, kv head) up to which t
 // 106, 16 of 64K to 256K at 8% 161 -> 140; even batches 285 -> 257 (24) or
 // unchanged (16, 32).  With fewer tiles the extra partials cost what the balance
 // gains (5 tiles: 20.3 -> 20.8).  1,536 and 2,048 workgroups measured within
-// 2% of 1,024.
+// 2% of 1,024.  Fewer sequences, whose proportional splits are many and so round
+// little, lose by them (attention with its combine, proportional / equal, us: 2 of
+// 500K to 1M tokens 115 / 119, 4 of 128K to 1M 120 / 123, 6 of 130K to 260K 69.5 /
+// 71.1, 8 of 250K 129 / 133; one gain, 8 of 128K to 256K 115 / 112), and 17 to 32
+// rows as often lose as gain (12 of 64K to 128K 85 / 95, 8 of 128K to 256K 120 / 132;
+// 16 of 64K to 256K 178 / 159, 32 of 64K to 128K 229 / 220).
 constexpr int kBatchWorkgroups = 1024;
 constexpr int kBatchTiles = 24;
 // Up to this many 32-token tiles per (sequence, KV head), with at most 16 rows,
