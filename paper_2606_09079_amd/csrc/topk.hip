@@ -735,7 +735,12 @@ topk_select_kernel(SeqTable t, const uint32_t* __restrict__ scores, int32_t* __r
 // less), a bin too large to pack is refined by digits over the registers, and
 // a thread emits 64 consecutive chunks.  Bound: instruction issue and latency
 // on one compute unit.  40,003 keys, 1,638 kept: 75 us with the streaming
-// topk_kernel, which reads the keys six times, 19 us here.
+// topk_kernel, which reads the keys six times, 19 us here.  A slot past the end
+// costs nearly what a key does, so the three sizes lie in about equal ratios from
+// 16 to 64: a call over 24,576 keys takes 16.3 us, 24,577 21.1, 40,960 22.9, 40,961
+// 31.4, 65,536 34.2, and 65,537 with the streaming kernel 128 (the recall over
+// three layers 55.5 and 300, although its masks exceed the scalar registers and
+// are kept in vector lanes).
 constexpr int kWideMaxN = 65536;
 
 template <int MODE, bool RECALL, int KPT>
