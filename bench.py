@@ -999,7 +999,7 @@ def bench_golden(args) -> int:
                    "golden_set_size_mean": round(float(golden.float().mean().cpu()), 1)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
-                     "kernel": "lsa_golden_labels (row, vote, compact kernels)", "avg_launch_us": round(call_us, 2),
+                     "kernel": "lsa_golden_labels (scan, row, exact, vote, compact kernels)", "avg_launch_us": round(call_us, 2),
                      "algorithmic_bytes_per_launch": int(call_bytes)},
     }
     if not args.no_cpu_baseline:

@@ -44,13 +44,12 @@
 //
 // What a window takes depends on its logits, as only rows whose set lies within
 // the listed entries are settled by the scan.  64 steps, 21 layers, 131,072
-// entries (705 MB), against reading every row three times: 1 entry in 256 far
-// above the others 449 -> 164 us (scan 120, rows 27, exact 4.5 with no row left
-// to it, votes 9, labels 5); the second half masked 394 -> 162; one row of those
-// open (about one window in ten) about 90 more, as one workgroup then reads it
-// alone; standard normal logits, every row open, 1,450 -> 510 to 910 (the two
-// reads of every row, from process to process); p = 0.9 of the peaked rows 800 ->
-// 690, p = 1 511 -> 450.
+// entries (705 MB), us, against reading every row three times: 1 entry in 256 far
+// above the others 452 -> 165 (scan 120, rows 27, exact 4.5 with no row left to it,
+// votes 9, labels 5); the second half masked 399 -> 163; one row of those open
+// (about one window in ten) about 90 more, as one workgroup then reads it alone;
+// standard normal logits, every row open, 1,450 to 1,850 -> 510 to 920 from process
+// to process; p = 0.9 of the peaked rows 451 -> 220, p = 1, every row open, 512 -> 443.
 #include "golden_geometry.h"
 #include "lsa_internal.h"
 
@@ -1016,9 +1015,9 @@ constexpr int kCountBits = 7;  // counts up to 127 >= LSA_MAX_GOLDEN_LAYERS
 // with four; 1,024: 8.7, 6.0; 512: 6.3, 6.6; 32: 4.6, 6.7, as half the wavefronts
 // take twice as long).
 constexpr int kVoteTwoSteps = 768;  // words of the longest row from which a thread takes two steps
-// Layers' words in flight at once; the last batch is padded.  4,096 words, 8, 21, 48
-// and 61 layers, us: 8 in flight 6.3, 8.9, 13.0, 15.7; 16 7.1, 9.0, 12.4, 14.8; 24 8.2,
-// 9.3, 12.8, 16.0; 32 9.5, 9.5, 14.7, 15.6.
+// Layers' words in flight at once; the last batch is padded.  4,096 words, 8, 21, 30,
+// 48 and 61 layers, us: 8 in flight 6.3, 9.0, 10.5, 12.9, 15.7; 16 7.0, 9.3, 9.9,
+// 12.8, 15.0; 24 8.2, 9.0, 12.0, 13.1, 16.0; 32 9.5, 9.5, 10.0, 14.7, 15.6.
 constexpr int kVoteBatch = 16;
 
 template <int kVoteSteps>

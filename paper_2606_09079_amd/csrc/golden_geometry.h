@@ -14,9 +14,10 @@ namespace lsa {
 // rows, us a call, peaked / flat logits, held against scanned: 2,500 entries
 // 29 / 33, 54 / 79; 8,192 36 / 52, 39 / 91; 16,384 48 / 74, 45 / 116; with 48
 // entries per thread (two workgroups per CU) 24,000 75 / 112, 56 / 134.  Past
-// 16,384 peaked rows lose more held than flat ones gain; flat rows of 16,385 to
-// 28,000 entries take 4 to 17% longer than three passes over them took (100, 125
-// us at 16,385 and 24,000), from 32,768 on less.
+// 16,384 peaked rows lose more held than flat ones gain.  Against three passes over
+// every row, peaked rows of 16,385 and 24,000 entries take 53 / 87 and 56 / 102 us,
+// flat ones 118 to 125 / 100 and 134 to 147 / 126, with p = 1 102 / 91 and 112 / 113;
+// from 32,768 entries on none takes longer.
 constexpr int kGoldenHeld = 32;
 constexpr int kGoldenDirectMax = 512 * kGoldenHeld;
 constexpr int kGoldenListMax = 2048;
